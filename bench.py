@@ -39,6 +39,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "tuned conv2d/matmul GFLOP/s + % fp32 roofline; measurements to reach best"
 PEAK_FP32_TFLOPS = 157.3      # MI355X published fp32 (vector and MFMA), dense
+# a split-operand kernel takes six bf16 MFMAs for each fp32 one: 1/6 of the
+# published dense bf16 rate
+PEAK_SPLIT_TFLOPS = 2516.6 / 6
 PEAK_HBM_GBS = 8000.0         # MI355X published HBM3E bandwidth
 TOL = 1e-4
 
@@ -88,15 +91,21 @@ FAMILY_NAME = {1: "conv_valu", 2: "conv_mfma", 3: "mm_valu", 4: "mm_mfma", 5: "c
 def kernel_name(space, idx):
     """Template instance the schedule selects (as rocprofv3 lists it)."""
     info = space.kernel_info(idx)
+    if info["family"] == 5 and info["nparams"] == 6:
+        return f"conv_split<{info['params'][0] // 2}, {info['params'][1] // 2}>"
     args = ", ".join(str(v) for v in info["params"][: info["nparams"]])
     return f"{FAMILY_NAME[info['family']]}<{args}>"
 
 
-def roof(flops, nbytes, seconds):
+def peak_tflops(kernel):
+    return PEAK_SPLIT_TFLOPS if kernel.startswith("conv_split") else PEAK_FP32_TFLOPS
+
+
+def roof(flops, nbytes, seconds, kernel):
     """(achieved flop/s, attainable, bound) of one kernel launch."""
-    ai = flops / nbytes
-    hbm_bound = ai * PEAK_HBM_GBS * 1e9 < PEAK_FP32_TFLOPS * 1e12
-    attainable = ai * PEAK_HBM_GBS * 1e9 if hbm_bound else PEAK_FP32_TFLOPS * 1e12
+    ai, peak = flops / nbytes, peak_tflops(kernel) * 1e12
+    hbm_bound = ai * PEAK_HBM_GBS * 1e9 < peak
+    attainable = ai * PEAK_HBM_GBS * 1e9 if hbm_bound else peak
     return flops / seconds, attainable, "hbm" if hbm_bound else "compute"
 
 
@@ -313,7 +322,8 @@ def main(argv=None):
         rows = []
         for i, task in enumerate(wk.T):
             res, m = task["res"], task["meas"]
-            ach, att, bound = roof(task["flops"], task["bytes"], m.median_ms * 1e-3)
+            ach, att, bound = roof(task["flops"], task["bytes"], m.median_ms * 1e-3,
+                                   task["kernel"])
             rows.append(dict(
                 name=task["name"], count=task["count"], shape=list(task["shape"]),
                 best_schedule=task["knobs"], kernel=task["kernel"],
@@ -349,16 +359,17 @@ def main(argv=None):
     j = max(range(len(W[head].T)), key=lambda i: W[head].T[i]["count"] * launch_ms[i])
     task = W[head].T[j]
     avg_ms = launch_ms[j]
-    ach, att, bound = roof(task["flops"], task["bytes"], avg_ms * 1e-3)
+    ach, att, bound = roof(task["flops"], task["bytes"], avg_ms * 1e-3, task["kernel"])
     if bound == "hbm":
         roofline = {"bound": "hbm", "achieved": round(task["bytes"] / (avg_ms * 1e-3) / 1e9, 1),
                     "peak": PEAK_HBM_GBS, "unit": "GB/s"}
     else:
         roofline = {"bound": "mfma" if task["knobs"].get("mfma", 0) else "alu",
-                    "achieved": round(ach / 1e12, 3), "peak": PEAK_FP32_TFLOPS,
+                    "achieved": round(ach / 1e12, 3),
+                    "peak": round(peak_tflops(task["kernel"]), 1),
                     "unit": "TFLOP/s"}
     roofline["frac"] = round(roofline["achieved"] / roofline["peak"], 4)
-    if roofline["unit"] == "TFLOP/s":
+    if roofline["unit"] == "TFLOP/s" and roofline["peak"] == PEAK_FP32_TFLOPS:
         roofline["mfma_ceiling"] = round(ceiling_tflops, 2)
         roofline["frac_of_ceiling"] = round(roofline["achieved"] / ceiling_tflops, 4)
     # A split schedule is two launches per layer (the kernel, then the reduce

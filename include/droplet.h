@@ -78,7 +78,10 @@ typedef struct ds_space ds_space;
  * chunk's quads between up to four wave groups of one workgroup (summed in
  * LDS) and the rest across workgroups; 3 the same over band tiles: th * tw
  * consecutive pixels of the output flattened over (image, row, column).  Only
- * band tiles may reach past the output's height or width.  matmul axes: bm,
+ * band tiles may reach past the output's height or width.  3x3 points of mfma 2
+ * and 3 at unroll depth 1 over whole groups of eight channels compute their
+ * fp32 products as six bf16 MFMAs of operands split into three bf16 values
+ * (24 bits; no less precise than the fp32 MFMA).  matmul axes: bm,
  * bn {16,...,256} (kept if <= M, N), bk {4,...,64} (kept if <= K), unroll,
  * dbuf {0,1}, mfma {0,1}, ks {1,2,4,8} (kept if <= K), vec {1,4} (floats per
  * lane of the operand loads).  The
@@ -142,7 +145,8 @@ typedef struct {
     int32_t valid;
     int32_t threads;      /* workgroup size */
     int64_t grid;         /* number of workgroups (1-D) */
-    int32_t lds_bytes;    /* dynamic LDS per workgroup */
+    int32_t lds_bytes;    /* dynamic LDS per workgroup (a split-operand launch uses its
+                             own layout: ds_kernel_info.lds_bytes) */
     int32_t acc;          /* fp32 accumulators per lane */
     int32_t unroll_eff;   /* unroll factor of the reduction loop (conv MFMA: the
                              number of 16-step groups read ahead, 1..3) */
@@ -175,7 +179,8 @@ enum {
     DS_KERNEL_CONV_MFMA = 2,  /* conv_mfma<TKB, NPB, D, LDS> (conv mfma = 1) */
     DS_KERNEL_MM_VALU = 3,    /* mm_valu<RM, RN, BK, UF, DB> */
     DS_KERNEL_MM_MFMA = 4,    /* mm_mfma<WM, WN, BK, UF, DB, KG> */
-    DS_KERNEL_CONV_MFMA2 = 5  /* conv_mfma2<TKB, NPB, U, KG> (conv mfma = 2 and 3) */
+    DS_KERNEL_CONV_MFMA2 = 5  /* conv_mfma2<TKB, NPB, U, KG, RC> (conv mfma = 2 and 3); with
+                                 a sixth parameter of 1, conv_split<TKB / 2, NPB / 2> */
 };
 
 /* The compiled program a valid schedule selects (Definition 1: an annotated

@@ -166,6 +166,11 @@ struct Conv2Args {
     int h_dc, h_dr;       // blockDim in (halo channel, unit) mixed radix
     FastDiv f_wru, f_hcu, f_hru, f_rs, f_s, f_tk, f_tq, f_tp, f_ksw;
     FastDiv f_q, f_p, f_hp, f_pq;   // band tiles: Q, P, hp, P*Q
+    // split-operand launch (conv_split)
+    int split;            // 1: that launch (0: fp32 MFMAs, the rest unused)
+    int sws, scs;         // halo row length, halo positions
+    int sxo;              // LDS bytes of the weight part
+    FastDiv f_sws;
 };
 
 // Launch shape of a conv_mfma2 point.
@@ -339,6 +344,36 @@ inline Conv2Shape conv2_setup(const int64_t *sh, int tk, int th, int tw, int tc,
     return g;
 }
 
+// Set-up of the split-operand launch (conv_split) of a conv_mfma2 point; false
+// when the point runs on fp32 MFMAs.  Who takes it:
+//   - unroll depth 1 and one wave group: the depth counts quads read ahead by
+//     the fp32 loop, which stays the program of every deeper point, so both
+//     stay in the search space;
+//   - 3x3 filters, whole 32-channel x 32-pixel blocks of four waves, and splits
+//     of whole groups of eight channels (what a plane's 16 bytes hold): with
+//     three channels padded to eight the fp32 loop is faster (3x64x224x224 at
+//     batch 16: 69 us against 72) and more precise;
+//   - at most two halo positions per thread: they are held in registers twice
+//     (next stage's planes, the one after in fp32) and all 256 are in use.
+constexpr int kConvSplitHalo = 2;         // halo units per thread of a stage
+constexpr int kConvSplitRow = 496;        // LDS bytes of a weight row: 10 taps of 48, and 16
+constexpr int kConvSplitSlots = 4;
+inline bool conv2_split_setup(Conv2Args &a, const Conv2Shape &c, int64_t *lds) {
+    a.split = 0;
+    if (a.R != 3 || a.S != 3 || c.u != 1 || c.kg != 1 || c.tkb < 2 || c.npb < 2 || c.npb > 4 ||
+        a.wpx != 4 || a.C % 8 != 0 || (int64_t(a.cps) * a.tc) % 8 != 0)
+        return false;
+    a.sws = ((a.band ? a.Q : a.tw) - 1) * a.st + a.S;
+    const int64_t nh = int64_t(a.hs) * a.sws;
+    if (nh > kConvSplitHalo * c.threads) return false;
+    a.split = 1;
+    a.scs = int(nh);
+    a.sxo = a.tk * kConvSplitRow;
+    a.f_sws = make_fastdiv(a.sws);
+    *lds = std::max<int64_t>(c.lds, a.sxo + 48 * nh);
+    return true;
+}
+
 // Tile rows per group of the matmul tile order: the power of two (at most
 // tiles_m) that minimises the A rows plus B columns, in elements, touched by
 // the contiguous tile range of one XCD (ties: the smaller), so that range is
@@ -388,6 +423,7 @@ int launch_plan(const Plan &plan, hipStream_t stream);
 const void *conv_valu_instance(int kpt, int ppt, int uf, int lds);
 const void *conv_mfma_instance(int tkb, int npb, int d, int lds);
 const void *conv_mfma2_instance(int tkb, int npb, int u, int kg, int rc);
+const void *conv_split_instance(int tkb, int npb);
 const void *mm_valu_instance(int rm, int rn, int bk, int uf, int dbuf);
 const void *mm_mfma_instance(int wm, int wn, int bk, int uf, int dbuf, int kg);
 int count_instances();

@@ -21,6 +21,7 @@ const Space &space_of(const ds_space *s);
 const void *g_conv_valu[kConvValuSlots];
 const void *g_conv_mfma[kConvMfmaSlots];
 const void *g_conv_mfma2[kConvMfma2Slots];
+const void *g_conv_split[kConvSplitSlots];
 const void *g_mm_valu[kMmValuSlots];
 const void *g_mm_mfma[kMmMfmaSlots];
 
@@ -428,6 +429,11 @@ const void *conv_mfma2_instance(int tkb, int npb, int u, int kg, int rc) {
     return g_conv_mfma2[(((a * 6 + b) * 3 + c) * 3 + d) * 2 + (rc == kConv2FewCopies)];
 }
 
+const void *conv_split_instance(int tkb, int npb) {
+    const int a = log2_exact(tkb) - 1, b = log2_exact(npb) - 1;
+    return a < 0 || a > 1 || b < 0 || b > 1 ? nullptr : g_conv_split[a * 2 + b];
+}
+
 const void *mm_valu_instance(int rm, int rn, int bk, int uf, int dbuf) {
     const int a = log2_exact(rm), b = log2_exact(rn), k = log2_exact(bk) - 2, c = log2_exact(uf);
     if (a < 0 || a > 4 || b < 0 || b > 4 || k < 0 || k > 4 || c < 0 || c > 6 || (dbuf & ~1))
@@ -449,6 +455,7 @@ int count_instances() {
     for (auto p : g_conv_valu) n += p != nullptr;
     for (auto p : g_conv_mfma) n += p != nullptr;
     for (auto p : g_conv_mfma2) n += p != nullptr;
+    for (auto p : g_conv_split) n += p != nullptr;
     for (auto p : g_mm_valu) n += p != nullptr;
     for (auto p : g_mm_mfma) n += p != nullptr;
     return n;
@@ -500,10 +507,17 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         plan.func = conv_mfma2_instance(c.tkb, c.npb, c.u, c.kg, a.rc);
         plan.family = DS_KERNEL_CONV_MFMA2;
         plan.nparams = 5;
-        const int pr[5] = {c.tkb, c.npb, c.u, c.kg, a.rc};
+        const int pr[6] = {c.tkb, c.npb, c.u, c.kg, a.rc, 1};
         std::memcpy(plan.params, pr, sizeof pr);
         plan.slot = (((log2_exact(c.tkb) * 6 + log2_exact(c.npb)) * 3 + log2_exact(c.u)) * 3 +
                      log2_exact(c.kg)) * 2 + (a.rc == kConv2FewCopies);
+        int64_t lds = 0;
+        if (conv2_split_setup(a, c, &lds)) {
+            plan.func = conv_split_instance(c.tkb, c.npb);
+            plan.nparams = 6;
+            plan.slot = kConvMfma2Slots + (log2_exact(c.tkb) - 1) * 2 + log2_exact(c.npb) - 1;
+            plan.lds = int(lds);
+        }
         plan.splits = a.ksw > 1 ? int(cdiv64(a.chunks, a.cps)) : 1;
         plan.y_elems = int64_t(a.N) * a.K * a.P * a.Q;
     } else if (s->op == DS_OP_CONV2D_NCHW) {

@@ -1,0 +1,481 @@
+// Split-operand 3x3 conv for gfx950 (conv mfma = 2 and 3 at unroll depth 1): fp32
+// products on the bf16 matrix cores.
+//
+// Every operand is written as the sum of three bf16 values, x = x0 + x1 + x2
+// (x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1): 24 bits, so the sum
+// is exact), and a product of two operands becomes the six products x_i * w_j
+// with i + j <= 2, each a v_mfma_f32_32x32x16_bf16 accumulating in fp32, the
+// smallest first.  What is left out is below 2^-24 of the product.  Six bf16
+// MFMAs take 6/16 of the cycles of the fp32 MFMAs they replace, and round less
+// often: against fp64 the error is 0.8 of the fp32 MFMA program's (3x3 over 64
+// channels: 3.6e-7 against 4.3e-7 of the result's 2-norm).
+//
+// A workgroup computes the tile of the fp32 program (conv_mfma2): tk channels x
+// th * tw pixels, four waves of 32 TB channels x 32 NB pixels.  Its reduction
+// runs in stages of eight channels; a stage's operands sit in LDS as bf16
+// planes, eight channels (16 bytes a plane, one MFMA operand) at a halo position
+// or weight tap, so the loop reads them with one ds_read_b128 each and the
+// splitting is done once per element instead of once per tap and wave.  An MFMA
+// step takes two taps (one per half-wave); the tenth tap is zero weights.
+//
+// What bounds it: the matrix cores at the clock that load leaves (1.9 GHz; the
+// library's bf16 product of 8192^2 matrices runs 1.13 PFLOP/s on the same card,
+// this loop 1.16 on 16x64x224x224, the padded tap included).  fp32 MFMAs hold
+// the vector unit, bf16 ones do not: 64 vector instructions between 32 of them
+// cost nothing, but only between MFMAs of the same wave, so the next stage is
+// split between the MFMAs of this one and kept in registers until the planes
+// in LDS are free.  Splitting it after the loop instead: 28x28x512 392 us, this
+// way 361.  VGG-16 at batch 16, against the fp32 program of the same schedule:
+// 64x224x224 532 -> 336 us, 512x28x28 (8 reduction splits, their reduce
+// included) 571 -> 351, 512x14x14 (16 splits) 177 -> 131.
+#include "kern_common.h"
+
+namespace ds {
+
+namespace {
+
+// The tile order, output and store rules below are those of conv_mfma2.
+__device__ __forceinline__ int fdv(int n, FastDiv f) {
+    return int((__umulhi(unsigned(n), f.m) + unsigned(n)) >> f.s);
+}
+
+// Tile of a workgroup (tile order: k, q, p, split, image): channel tile kt,
+// pixel tile (pt, qt) of image n, split z over chunks [ci0, ci1).  A band tile
+// starts at pixel qt * npx of the flattened output: image n0, padded row g0 of
+// that image; its halo is the `rows` padded rows from there (image boundaries
+// included), each one whole output row wide.
+struct Tile {
+    int kt, qt, pt, n, z, ci0, ci1, n0, g0, rows;
+    __device__ __forceinline__ explicit Tile(const Conv2Args &a) {
+        const int t0 = xcd_tile(blockIdx.x, gridDim.x);
+        const int t1 = fdv(t0, a.f_tk);
+        kt = t0 - t1 * a.tiles_k;
+        const int t2 = fdv(t1, a.f_tq);
+        qt = t1 - t2 * a.tiles_q;
+        const int t3 = fdv(t2, a.f_tp);
+        pt = t2 - t3 * a.tiles_p;
+        n = fdv(t3, a.f_ksw);
+        z = t3 - n * a.ksw;
+        ci0 = z * a.cps;
+        ci1 = min(ci0 + a.cps, a.chunks);
+        n0 = n;
+        g0 = 0;
+        rows = a.hs;
+        if (a.band) {
+            const int f0 = qt * a.npx, fl = min(f0 + a.npx, a.F) - 1;
+            const int r0 = fdv(f0, a.f_q), rl = fdv(fl, a.f_q);
+            n0 = fdv(r0, a.f_p);
+            const int nl = fdv(rl, a.f_p);
+            g0 = (r0 - n0 * a.P) * a.st;
+            rows = (nl - n0) * a.hp + (rl - nl * a.P) * a.st + a.R - g0;
+        }
+    }
+};
+
+// Output of the tile's image (the split's partial output when ksw > 1).
+__device__ __forceinline__ float *out_base(const Conv2Args &a, const Tile &T) {
+    const int PQ = a.P * a.Q;
+    return (a.ksw > 1 ? a.part + (size_t)T.z * a.N * a.K * PQ : a.y) + (size_t)T.n * a.K * PQ;
+}
+
+// Stores 4 consecutive tile pixels, from pix on, of output channel k.
+__device__ __forceinline__ void put(const Conv2Args &a, const Tile &T, float *yn, int k, int pix,
+                                    floatx4 val) {
+    const int PQ = a.P * a.Q;
+    if (k >= a.K) return;
+    if (a.band) {
+        const int f = T.qt * a.npx + pix;
+        if (a.st4 && f + 3 < a.F) {
+            const int img = fdv(f, a.f_pq);
+            *reinterpret_cast<floatx4 *>(yn + (size_t)img * a.K * PQ + (size_t)k * PQ +
+                                         (f - img * PQ)) = val;
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int fe = f + e;
+            if (fe >= a.F) break;
+            const int img = fdv(fe, a.f_pq);
+            yn[(size_t)img * a.K * PQ + (size_t)k * PQ + (fe - img * PQ)] = val[e];
+        }
+    } else {
+        const int py = pix >> a.ltw, px = pix & (a.tw - 1);
+        const int p = T.pt * a.th + py, q = T.qt * a.tw + px;
+        if (a.st4 && p < a.P && q + 3 < a.Q) {
+            *reinterpret_cast<floatx4 *>(yn + (size_t)k * PQ + p * a.Q + q) = val;
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int pe = T.pt * a.th + ((pix + e) >> a.ltw), qe = T.qt * a.tw + ((pix + e) & (a.tw - 1));
+            if (pe < a.P && qe < a.Q) yn[(size_t)k * PQ + pe * a.Q + qe] = val[e];
+        }
+    }
+}
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+    const bf16x2 r = {(__bf16)a, (__bf16)b};
+    unsigned p = __builtin_bit_cast(unsigned, r);
+    // keeps the conversion of the pair from being repeated for one half
+    __asm__("" : "+v"(p));
+    return p;
+}
+
+// The three bf16 planes of two floats (each plane packed in one word).
+__device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[3]) {
+    p[0] = pack_bf16(x, y);
+    x -= __uint_as_float(p[0] << 16);
+    y -= __uint_as_float(p[0] & 0xffff0000u);
+    p[1] = pack_bf16(x, y);
+    x -= __uint_as_float(p[1] << 16);
+    y -= __uint_as_float(p[1] & 0xffff0000u);
+    p[2] = pack_bf16(x, y);
+}
+
+// The three bf16 planes of the eight channels of a unit, 16 bytes each.
+struct Planes {
+    uintx4 q[3];
+};
+__device__ __forceinline__ void split_unit(const float (&v)[8], Planes &o) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        unsigned p[3];
+        split_pair(v[2 * j], v[2 * j + 1], p);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) o.q[i][j] = p[i];
+    }
+}
+__device__ __forceinline__ void store_unit(char *dst, const Planes &o) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) *reinterpret_cast<uintx4 *>(dst + 16 * i) = o.q[i];
+}
+
+// Workgroup barrier for LDS only: loads from global memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int TB, int NB>
+__global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
+    constexpr int HU = kConvSplitHalo, WU = (32 * TB * 9 + 255) / 256, U = HU + WU;
+    constexpr int STEPS = 5;                      // 9 taps, two a step
+    constexpr int ROWB = kConvSplitRow;
+    extern __shared__ float smem[];
+    char *lds = reinterpret_cast<char *>(smem);
+    const Tile T(a);
+    if (T.ci0 >= T.ci1) return;
+
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int lane = tid & 63;
+    const int wp = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lg = lane >> 5;
+    const int HW = a.H * a.W;
+    const int hy0 = T.pt * a.th * a.st - a.pd;
+    const int hx0 = (a.band ? 0 : T.qt * a.tw * a.st) - a.pd;
+    const int kvalid = a.K - T.kt * a.tk;
+    const int c_beg = T.ci0 * a.tc, c_end = min(T.ci1 * a.tc, a.C);
+    const int stages = (c_end - c_beg) >> 3;
+    const char *xb = reinterpret_cast<const char *>(a.x + ((size_t)T.n0 * a.C + c_beg) * HW);
+    const char *wb = reinterpret_cast<const char *>(a.w + ((size_t)T.kt * a.tk * a.C + c_beg) * 9);
+    const int nh = a.scs, nw = a.tk * 9;
+
+    // Source (byte offset from the stage's first channel; -1: outside the
+    // image) and LDS position of this thread's units; a unit is eight channels
+    // at one halo position or one weight tap.  Threads past the last unit
+    // repeat it.
+    int src[U], dw[WU];
+#pragma unroll
+    for (int u = 0; u < HU; ++u) {
+        const int e = min(u * nthr + tid, nh - 1);
+        const int hy = fdv(e, a.f_sws), hx = e - hy * a.sws;
+        int gy, img = 0;
+        if (a.band) {
+            const int gr = T.g0 + hy;
+            img = fdv(gr, a.f_hp);
+            gy = gr - img * a.hp - a.pd;
+        } else {
+            gy = hy0 + hy;
+        }
+        const int gx = hx0 + hx;
+        const bool in = hy < T.rows && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+        src[u] = in ? 4 * ((img * a.C * a.H + gy) * a.W + gx) : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < WU; ++u) {
+        const int e = min(u * nthr + tid, nw - 1);
+        const int row = e / 9, t = e - row * 9;
+        src[HU + u] = 4 * (min(row, kvalid - 1) * a.C * 9 + t);
+        dw[u] = row * ROWB + 48 * t;
+    }
+    auto dst = [&](int u) {
+        return lds + (u < HU ? a.sxo + 48 * min(u * nthr + tid, nh - 1) : dw[max(u - HU, 0)]);
+    };
+    float raw[U][8];
+    // unit u of stage s; past the last stage every lane reads one address
+    auto load = [&](int u, int s) {
+        const int on = s < stages ? -1 : 0;
+        const char *b = u < HU ? xb + (size_t)(s & on) * 8 * HW * 4 : wb + (size_t)(s & on) * 8 * 9 * 4;
+        const unsigned o = unsigned(max(src[u], 0) & on);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            raw[u][j] = *reinterpret_cast<const float *>(b + (u < HU ? (size_t)j * HW * 4 : j * 9 * 4) + o);
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u, 0);
+
+    // zeros: halo positions outside the image, the weights of the padding tap
+#pragma unroll
+    for (int u = 0; u < HU; ++u)
+        if (src[u] < 0) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                *reinterpret_cast<uintx4 *>(dst(u) + 16 * i) = uintx4{0u, 0u, 0u, 0u};
+        }
+    for (int e = tid; e < 3 * a.tk; e += nthr) {
+        const int row = e / 3, k = e - row * 3;
+        *reinterpret_cast<uintx4 *>(lds + row * ROWB + 48 * 9 + 16 * k) = uintx4{0u, 0u, 0u, 0u};
+    }
+
+    // lane bases (bytes), and the offset of step t's tap 2t + lg from a
+    // pixel's halo position (the padding tap: the last one's)
+    int bb[NB], off[STEPS / 2 + 1];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int pix = (wp * NB + b) * 32 + li;
+        int pos;
+        if (a.band) {
+            const int f = min(T.qt * a.npx + pix, a.F - 1);
+            const int r = fdv(f, a.f_q), q = f - r * a.Q;
+            const int img = fdv(r, a.f_p), p = r - img * a.P;
+            pos = ((img - T.n0) * a.hp + p * a.st - T.g0) * a.sws + q * a.st;
+        } else {
+            const int py = pix >> a.ltw, px = pix & (a.tw - 1);
+            pos = py * a.st * a.sws + px * a.st;
+        }
+        bb[b] = a.sxo + 48 * pos;
+    }
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+        const int u0 = 2 * t, u1 = cmin(2 * t + 1, 8);
+        const int o = 48 * (lg ? u1 / 3 * a.sws + u1 % 3 : u0 / 3 * a.sws + u0 % 3);
+        if (t & 1) off[t / 2] |= o << 16;      // both below 2^15: halos of at most 512 positions
+        else off[t / 2] = o;
+    }
+    const int ab = li * ROWB + 48 * lg;
+
+    floatx16 acc[TB][NB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[i][b] = floatx16{};
+
+    struct Ops {
+        bf16x8 A[TB][3], B[NB][3];
+    };
+    auto read = [&](int t, Ops &o) {
+#pragma unroll
+        for (int i = 0; i < TB; ++i)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                o.A[i][k] = *reinterpret_cast<const bf16x8 *>(lds + ab + i * 32 * ROWB + 96 * t + 16 * k);
+        const int ot = t & 1 ? off[t / 2] >> 16 : off[t / 2] & 0xffff;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                o.B[b][k] = *reinterpret_cast<const bf16x8 *>(lds + bb[b] + ot + 16 * k);
+    };
+    auto mma = [&](const Ops &o) {
+        constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+        for (int e = 0; e < 6; ++e)
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.A[i][pa[e]], o.B[b][pb[e]],
+                                                                        acc[i][b], 0, 0, 0);
+    };
+    Planes pl[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        split_unit(raw[u], pl[u]);
+        load(u, 1);
+    }
+    for (int s = 0; s < stages; ++s) {
+        if (s > 0) lds_barrier();       // every wave is past its reads of the last stage
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u >= HU || src[u] >= 0) store_unit(dst(u), pl[u]);
+        lds_barrier();
+        // each step's MFMAs, with the split of one unit of the next stage and
+        // the loads of the one after it between them
+        Ops o[2];
+        read(0, o[0]);
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            if (t + 1 < STEPS) read(t + 1, o[(t + 1) & 1]);
+            if (t < U) {
+                split_unit(raw[t], pl[t]);
+                load(t, s + 2);
+            }
+            mma(o[t & 1]);
+            constexpr int NM = 6 * TB * NB;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (m < 3 * (TB + NB)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                if (m >= NM - 8) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    // Infinities, NaN and values that round up past bf16's largest leave NaN in
+    // the accumulators, and the bf16 MFMA flushes denormal planes, which counts
+    // only where whole tiles are tiny: such tiles run again on fp32 MFMAs.
+    float nan = 0.f, big = 0.f;
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                nan = fmaf(acc[i][b][v], 0.f, nan);
+                big = fmaxf(big, fabsf(acc[i][b][v]));
+            }
+    const bool bad = !(nan == 0.f) || (big > 0.f && big < 0x1p-80f);
+    lds_barrier();
+    if (__any(bad)) {
+        if (lane == 0) reinterpret_cast<int *>(lds)[wp] = 1;
+    } else if (lane == 0) {
+        reinterpret_cast<int *>(lds)[wp] = 0;
+    }
+    lds_barrier();
+    int again = 0;
+    for (int w = 0; w < a.wpx; ++w) again |= reinterpret_cast<const int *>(lds)[w];
+    lds_barrier();
+    if (__builtin_amdgcn_readfirstlane(again)) {
+        // the lane's coordinates anew, so that nothing of this path is kept in
+        // registers through the loop above
+        int ln = lane;
+        __asm__ volatile("" : "+v"(ln));
+        const int lj = ln & 31, lh = ln >> 5;
+#pragma unroll
+        for (int i = 0; i < TB; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[i][b] = floatx16{};
+        const float *pw[TB], *px[NB];
+        int at[NB];
+        unsigned ok[NB];                          // bit t: tap t is inside the image
+#pragma unroll
+        for (int i = 0; i < TB; ++i)
+            pw[i] = a.w + ((size_t)(T.kt * a.tk + min(i * 32 + lj, kvalid - 1)) * a.C + c_beg + lh) * 9;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int pix = (wp * NB + b) * 32 + lj;
+            int img = T.n, p, q;
+            if (a.band) {
+                const int f = min(T.qt * a.npx + pix, a.F - 1), r = fdv(f, a.f_q);
+                q = f - r * a.Q;
+                img = fdv(r, a.f_p);
+                p = r - img * a.P;
+            } else {
+                p = T.pt * a.th + (pix >> a.ltw);
+                q = T.qt * a.tw + (pix & (a.tw - 1));
+            }
+            const int y0 = p * a.st - a.pd, x0 = q * a.st - a.pd;
+            px[b] = a.x + ((size_t)img * a.C + c_beg + lh) * HW;
+            at[b] = y0 * a.W + x0;
+            ok[b] = 0;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int y = y0 + t / 3, x = x0 + t % 3;
+                ok[b] |= unsigned(y >= 0 && y < a.H && x >= 0 && x < a.W) << t;
+            }
+        }
+        for (int c = 0; c < 8 * stages; c += 2) {
+            float A[TB][9], B[NB][9];
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int t = 0; t < 9; ++t) A[i][t] = pw[i][c * 9 + t];
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const bool in = ok[b] >> t & 1;
+                    const float v = px[b][(size_t)c * HW + (in ? at[b] + t / 3 * a.W + t % 3 : 0)];
+                    B[b][t] = in ? v : 0.f;
+                }
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int i = 0; i < TB; ++i)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i][t], B[b][t], acc[i][b],
+                                                                        0, 0, 0);
+        }
+    }
+
+    // Output through LDS, 16 channels x up to 64 pixels of a wave at a time, as
+    // in conv2_body.  A 32x32 block leaves lane (lg, li) rows 8*(v/4) + 4*lg +
+    // v%4 of column li.
+    constexpr int BG = NB < 2 ? NB : 2;
+    constexpr int ROW = 32 * BG + 4;
+    constexpr int LPR = 8 * BG;
+    float *stage = smem + wp * (16 * 68);
+    float *yn = out_base(a, T);
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int b0 = 0; b0 < NB; b0 += BG)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int b = 0; b < BG; ++b)
+#pragma unroll
+                    for (int v = 0; v < 8; ++v)
+                        stage[(8 * (v / 4) + 4 * lg + v % 4) * ROW + b * 32 + li] =
+                            acc[i][b0 + b][8 * h + v];
+#pragma unroll
+                for (int r0 = 0; r0 < 16; r0 += 64 / LPR) {
+                    const int row = r0 + lane / LPR, c4 = lane % LPR;
+                    const floatx4 val = *reinterpret_cast<const floatx4 *>(stage + row * ROW + 4 * c4);
+                    put(a, T, yn, T.kt * a.tk + i * 32 + h * 16 + row,
+                            (wp * NB + b0) * 32 + 4 * c4, val);
+                }
+            }
+}
+
+}  // namespace
+
+// Slot: log2(TB) * 2 + log2(NB)
+extern const void *g_conv_split[kConvSplitSlots];
+
+namespace {
+
+// Two waves per SIMD (256 registers): the operands of a step are read while the
+// step before multiplies.  Three waves without that ran slower (28x28x512:
+// 363 us against 379 us; 14x14x512: 137 us against 147 us).
+struct Registrar {
+    Registrar() {
+        g_conv_split[0] = reinterpret_cast<const void *>(&conv_split<1, 1>);
+        g_conv_split[1] = reinterpret_cast<const void *>(&conv_split<1, 2>);
+        g_conv_split[2] = reinterpret_cast<const void *>(&conv_split<2, 1>);
+        g_conv_split[3] = reinterpret_cast<const void *>(&conv_split<2, 2>);
+    }
+};
+const Registrar registrar;
+
+}  // namespace
+
+}  // namespace ds

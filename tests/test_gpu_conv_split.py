@@ -1,0 +1,146 @@
+"""The split-operand conv launch (conv mfma 2 and 3 at unroll depth 1, 3x3
+filters, whole groups of eight channels) on the GPU.
+
+* Small-integer inputs: bit-exact against the oracle (every plane product and
+  partial sum is an integer below 2**24), outputs all written, nothing past
+  the end; shapes with ragged K, odd image sizes, padding 0 and 2, bands
+  across images and reduction splits.
+* Precision: its error against the fp64 oracle is no larger than that of the
+  fp32-MFMA program of the same tile (a deeper unroll), on inputs of several
+  scales.  Both errors are sums of rounding errors of the same kind, so the
+  ratio of their 2-norms over thousands of outputs is stable; 1.1 leaves room
+  for its spread.
+* Values the bf16 planes cannot hold (infinities, NaN, floats that round past
+  the largest bf16, tiles of tiny values): the same outputs as the fp32
+  program, non-finite where and as it has them.
+"""
+import numpy as np
+import pytest
+
+import synthdata
+from oracle import kernels as ok
+
+pytestmark = pytest.mark.gpu
+
+CANARY = 12345.0
+TAIL = 64
+
+# shape, tile knobs (tk, th, tw, tc, ks, mfma)
+POINTS = [
+    ((2, 32, 28, 28, 64, 3, 3, 1, 1), (64, 16, 16, 4, 1, 2)),
+    ((2, 16, 30, 33, 70, 3, 3, 1, 1), (64, 8, 16, 8, 1, 2)),
+    ((1, 8, 20, 18, 33, 3, 3, 1, 0), (32, 16, 16, 4, 1, 2)),
+    ((1, 24, 19, 17, 40, 3, 3, 1, 2), (32, 8, 16, 8, 1, 2)),
+    ((3, 64, 14, 14, 96, 3, 3, 1, 1), (64, 16, 8, 4, 8, 3)),
+    ((5, 16, 9, 9, 64, 3, 3, 1, 1), (64, 16, 16, 4, 2, 3)),
+    ((2, 40, 13, 11, 48, 3, 3, 1, 1), (32, 16, 8, 4, 1, 3)),
+    ((1, 48, 12, 40, 32, 3, 3, 1, 1), (32, 4, 64, 4, 2, 3)),
+]
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from paper_2406_20037_amd import _lib
+    return torch, _lib
+
+
+def points(L, sh, knobs):
+    """(space, the split-operand schedule, an fp32-MFMA schedule of its tile)."""
+    tk, th, tw, tc, ks, mfma = knobs
+    space = L.Space(L.DS_OP_CONV2D_NCHW, sh)
+    kn = dict(tk=tk, th=th, tw=tw, tc=tc, unroll=0, lds=1, ks=ks, mfma=mfma, vec=1)
+    split = space.sched_of(**kn)
+    if not space.valid(split.index()):
+        split = space.sched_of(**dict(kn, vec=4))
+    info = space.kernel_info(split.index())
+    assert info["params"][5:] == [1], (sh, kn, info)
+    # a deeper unroll of the same tile and split runs on fp32 MFMAs
+    for ch in (8, 16, 32):
+        for unroll in (16, 64, 512):
+            for vec in (4, 1):
+                f32 = space.sched([vals.index(v) if v in vals else -1 for vals, v in zip(
+                    space.values, dict(kn, tc=ch, unroll=unroll, vec=vec).values())])
+                if -1 not in f32.index() and space.valid(f32.index()) and len(
+                        space.kernel_info(f32.index())["params"]) == 5:
+                    return space, split, f32
+    raise AssertionError(sh)
+
+
+def run(torch, L, s, x, w, n):
+    y = torch.full((n + TAIL,), float("nan"), device="cuda:0")
+    y[n:] = CANARY
+    L.kernel_run(L.DS_OP_CONV2D_NCHW, s, x, w, y)
+    torch.cuda.synchronize()
+    assert bool((y[n:] == CANARY).all()), "write past the end of y"
+    return y[:n].cpu().numpy().astype(np.float64)
+
+
+def dev(torch, a, shift=0):
+    buf = torch.zeros(a.size + shift, dtype=torch.float32, device="cuda:0")
+    buf[shift:] = torch.from_numpy(np.ascontiguousarray(a).ravel()).to("cuda:0")
+    return buf[shift:]
+
+
+IDS = ["x".join(map(str, p[0])) for p in POINTS]
+
+
+@pytest.mark.parametrize("sh,knobs", POINTS, ids=IDS)
+def test_split_bit_exact_on_integers(env, sh, knobs):
+    torch, L = env
+    _, split, _ = points(L, sh, knobs)
+    x, w = synthdata.conv_inputs(sh, "int")
+    ref = ok.conv2d_f64(x, w, sh).ravel()
+    for shift in (0, 1):
+        print("conv split int", sh, knobs, shift, flush=True)
+        got = run(torch, L, split, dev(torch, x, shift), dev(torch, w, shift), ref.size)
+        assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-12, 1e15])
+@pytest.mark.parametrize("sh,knobs", POINTS, ids=IDS)
+def test_split_no_less_precise_than_fp32_mfma(env, sh, knobs, scale):
+    torch, L = env
+    _, split, f32 = points(L, sh, knobs)
+    x, w = synthdata.conv_inputs(sh, "he")
+    x = (x * np.float32(scale)).astype(np.float32)
+    ref = ok.conv2d_f64(x, w, sh).ravel()
+    xd, wd = dev(torch, x), dev(torch, w)
+    print("conv split precision", sh, knobs, scale, flush=True)
+    e = [np.linalg.norm(run(torch, L, s, xd, wd, ref.size) - ref) for s in (split, f32)]
+    print(f"  error {e[0] / np.linalg.norm(ref):.3g}, fp32 MFMA {e[1] / np.linalg.norm(ref):.3g}")
+    assert e[0] <= 1.1 * e[1]
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "max", "tiny", "winf"])
+def test_split_special_values(env, kind):
+    torch, L = env
+    sh, knobs = POINTS[0]
+    _, split, f32 = points(L, sh, knobs)
+    x, w = synthdata.conv_inputs(sh, "he")
+    at = (1, 5, 13, 9)
+    if kind == "inf":
+        x[at] = np.inf
+        x[0, 0, 0, 0] = -np.inf
+    elif kind == "nan":
+        x[at] = np.nan
+    elif kind == "max":       # rounds past the largest bf16, the products stay finite
+        x[at] = 3.4e38
+        w *= np.float32(0.25)
+    elif kind == "tiny":      # the planes past the first are denormal
+        x *= np.float32(1e-36)
+    else:
+        w[3, 2, 1, 1] = np.inf
+    n = sh[0] * sh[4] * sh[2] * sh[3]
+    xd, wd = dev(torch, x), dev(torch, w)
+    print("conv split special", kind, flush=True)
+    got, want = (run(torch, L, s, xd, wd, n) for s in (split, f32))
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)
+    # both within fp32 rounding of the same sums: 288 terms, each below the
+    # tile's largest output
+    scale = np.abs(want[fin]).max()
+    assert np.abs(got[fin] - want[fin]).max() <= 288 * 2.0 ** -24 * scale
