@@ -818,11 +818,11 @@ constexpr int kConv2Waves2[] = {
 constexpr int kConv2FewWaves6[] = {
     10111, 10112, 10114, 10121, 10122, 10124, 10141, 10142, 10144, 10211, 10212, 10214,
     10221, 10222, 10224, 10241, 10242, 10244, 10411, 10412, 10414, 10421, 10422, 10424,
-    20111, 20112, 20114, 20121, 20122, 20124, 20141, 20142, 20144, 20211, 20212, 20214,
+    20111, 20112, 20114, 20141, 20142, 20144, 20211, 20212, 20214,
     20221, 20222, 20224, 20241, 20242, 20244, 40111, 40112, 40114, 40121, 40122, 40124,
     40141, 40142, 40144, 40211, 40212};
 constexpr int kConv2FewWaves5[] = {
-    10441, 10442, 10444, 10811, 10812, 20411, 20412};
+    10441, 10442, 10444, 10811, 10812, 20121, 20122, 20124, 20411, 20412};
 constexpr int kConv2FewWaves4[] = {
     40221, 40222, 40411, 40412};
 constexpr int kConv2FewWaves3[] = {
@@ -852,6 +852,17 @@ constexpr int conv2_waves(int tkb, int npb, int u, int kg, int rc) {
     for (int k : kConv2Waves2)
         if (k == key) return 2;
     return 1;
+}
+
+// Instances with the row-wise loops: the small tiles, whose steps have few MFMAs
+// beside their address arithmetic (one MFMA against 2.5 vector and 5 scalar
+// instructions in <1, 1, 4, 4>, now 0.5 and 0.6).  Larger ones spill under their
+// launch bounds with the addresses those loops hold.  Measured: 5x5 over 37
+// channels, batch 3, 61x53 (<1, 2, 1, 1>) 69.0 -> 47.7 us; ResNet-50's 3x3 stride
+// 2 over 512 channels at batch 1 (<2, 1, 1, 2>) 15.9 -> 14.9; 3x3 over 64
+// channels, 56x56 (<1, 1, 4, 4>) 9.74 -> 9.38.
+constexpr bool conv2_rows(int tkb, int npb, int u) {
+    return tkb * npb <= 2 && u * tkb * npb <= 4;
 }
 
 template <int TKB, int NPB, int U, int KG, int RC>
@@ -1095,15 +1106,81 @@ __global__ __launch_bounds__(256 * KG, conv2_waves(TKB, NPB, U, KG, RC)) void co
                     }
         };
         Ops o[2];
-        load(0, o[0]);
-        int j = 0;
-        for (; j + 2 <= tg; j += 2) {
-            load(j + 1, o[1]);
-            mma(o[0]);
-            load(j + 2, o[0]);
-            mma(o[1]);
+        // The steps of an S x S filter, a row of S taps at a time: the taps of a
+        // row are immediate offsets from one LDS address per operand block, moved
+        // on once a row.  An fp32 MFMA holds the vector unit, so the addition per
+        // operand read that steps of any filter need costs MFMA time, and their
+        // divisions outweigh a small tile's MFMAs.
+        auto rows = [&]<int S>(std::integral_constant<int, S>) {
+            constexpr int SA = 4 * KG * S * S;             // floats per quad step of A
+            const int nrow = (a.t4 / (KG * U)) * S;
+            int pa[TKB], pb[U][NPB];
+#pragma unroll
+            for (int i = 0; i < TKB; ++i) pa[i] = ab + i * 16 * a.wrow + 4 * g * S * S;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int b = 0; b < NPB; ++b) pb[u][b] = bb[b] + 4 * g * a.cs + u * sb;
+            auto tap = [&](int s, Ops &o) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+#pragma unroll
+                    for (int i = 0; i < TKB; ++i) o.A[u][i] = buf[pa[i] + s + u * SA];
+#pragma unroll
+                    for (int b = 0; b < NPB; ++b) o.B[u][b] = buf[pb[u][b] + s];
+                }
+            };
+            int r = 0, left = nrow;
+            auto row = [&]<int P>(std::integral_constant<int, P>) {
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    Ops &nx = o[(P * S + s + 1) & 1];
+                    if (s + 1 < S) {
+                        tap(s + 1, nx);
+                    } else {
+                        // past the last row: that row's first tap again (never multiplied)
+                        const bool end = --left == 0, wrap = ++r == S;
+                        r = wrap ? 0 : r;
+                        const int da = end ? 0 : wrap ? U * SA - (S - 1) * S : S;
+                        const int db = end ? 0 : wrap ? U * sb - (S - 1) * a.ws : a.ws;
+#pragma unroll
+                        for (int i = 0; i < TKB; ++i) pa[i] += da;
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int b = 0; b < NPB; ++b) pb[u][b] += db;
+                        tap(0, nx);
+                    }
+                    mma(o[(P * S + s) & 1]);
+                }
+            };
+            tap(0, o[0]);
+            while (left >= 2) {
+                row(std::integral_constant<int, 0>{});
+                row(std::integral_constant<int, 1>{});
+            }
+            if (left > 0) row(std::integral_constant<int, 0>{});
+        };
+        auto steps = [&]() {
+            load(0, o[0]);
+            int j = 0;
+            for (; j + 2 <= tg; j += 2) {
+                load(j + 1, o[1]);
+                mma(o[0]);
+                load(j + 2, o[0]);
+                mma(o[1]);
+            }
+            if (j < tg) mma(o[0]);
+        };
+        if constexpr (conv2_rows(TKB, NPB, U)) {
+            const int sq = a.R == a.S ? a.S : 0;
+            if (sq == 3) rows(std::integral_constant<int, 3>{});
+            else if (sq == 1) rows(std::integral_constant<int, 1>{});
+            else if (sq == 5) rows(std::integral_constant<int, 5>{});
+            else steps();
+        } else {
+            steps();
         }
-        if (j < tg) mma(o[0]);
     }
 
     // wave groups 1..KG-1 hand their partial tiles to group 0 through LDS
