@@ -597,6 +597,10 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         a.vecA = vec == 4 && (a.K % 4 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0);
         a.vecB = vec == 4 && (a.N % 4 == 0) && (reinterpret_cast<uintptr_t>(w) % 16 == 0);
         a.direct = a.vecA && a.vecB && a.M % bm == 0 && a.N % bn == 0 && a.K % bk == 0;
+        a.pipe = int64_t(std::min(a.M, bm)) * a.K < (int64_t(1) << 30) &&
+                         int64_t(bk) * a.N < (int64_t(1) << 30)
+                     ? (a.vecA && a.vecB ? 4 : 1)
+                     : 0;
         a.gm = mm_group_rows(a.tiles_m, a.tiles_n, a.ks, bm, bn);
         plan.func = mfma ? mm_mfma_instance(g.t0, g.t1, bk, g.unroll_eff, dbuf, kg)
                          : mm_valu_instance(g.t0, g.t1, bk, g.unroll_eff, dbuf);

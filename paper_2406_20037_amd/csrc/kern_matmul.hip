@@ -6,13 +6,15 @@
 //               j ^ swz(r), so the 16-byte reads of eight consecutive rows at
 //               one k land on distinct banks without padding,
 //   Bs[BK][BN]  n contiguous.
-// When every tile is full and the operands are 16-byte aligned (a.direct), the
-// K-tiles travel straight from global memory into LDS (global_load_lds, no
-// register staging); with dbuf the next ST-1 K-tiles are in flight while the
-// current one is consumed (ST = 3 stages when they fit in LDS, else 2).
-// Otherwise tiles are staged through registers with bounds checks (zero
-// outside A and B) and, with dbuf, written to the other LDS stage after the
-// current one is consumed.
+// MFMA tiles with two or more stages run pipelined (mm_mfma_pipe): K-tiles travel
+// straight from global memory into LDS (global_load_lds, no register staging),
+// 16 bytes per lane when rows of A and B are whole aligned 16-byte groups, else
+// 4, and the next ST-1 K-tiles are in flight while the current one is consumed
+// (ST = 3 stages when they fit in LDS, else 2).  The other kernels do the same
+// without the pipelined reads when every tile is also full (a.direct), and
+// otherwise stage tiles through registers with bounds checks (zero outside A
+// and B), written with dbuf to the other LDS stage after the current one is
+// consumed.
 //
 //   mm_valu: VALU FMA; thread (ty, tx) of a 16x16 grid owns RM rows x RN
 //            columns (contiguous).
@@ -355,19 +357,27 @@ struct MfmaShape {
     static constexpr int NV = BIG ? 16 : 4;           // accumulator values per lane
 };
 
-// Whether the direct path runs software-pipelined (mm_mfma_pipe): at least
-// two stages, every thread issuing the same number of copies per K-tile, and
-// at least two chunks per K-tile.
-template <int WM, int WN, int BK, int DB, int KG>
+// Whether K-tiles run software-pipelined (mm_mfma_pipe) with copies of W floats
+// per lane: at least two stages, every thread issuing the same number of copies
+// per K-tile, few enough for the wait counters (63) with two tiles in flight,
+// and at least two chunks per K-tile.
+template <int WM, int WN, int BK, int DB, int KG, int W>
 constexpr bool mm_pipelined() {
     using S = MfmaShape<WM, WN, BK, KG>;
     constexpr int BM = 2 * WM, BN = 2 * WN, NT = 256 * KG;
-    return mm_stages(BM, BN, BK, DB) >= 2 && (BM * BK / 4) % NT == 0 && (BK * BN / 4) % NT == 0 &&
-           S::NCH >= 2;
+    return mm_stages(BM, BN, BK, DB) >= 2 && (BM * BK / W) % NT == 0 && (BK * BN / W) % NT == 0 &&
+           (BM + BN) * BK / W / NT <= 32 && S::NCH >= 2;
 }
 
-// Direct (global -> LDS) K-loop with the LDS operand reads software-pipelined
-// across MFMA chunks.  A chunk is one k step of every MFMA block of the wave
+// K-loop of global -> LDS copies, W floats per lane, with the LDS operand reads
+// software-pipelined across MFMA chunks.  Rows of A past M and columns of B past
+// N re-read the last one (their outputs are not stored); in the last K-tile,
+// when K does not fill it, positions past K are written as zeros instead of
+// copied.  W = 1 takes any alignment.  Bound by the MFMAs, which hold the vector
+// unit: every vector instruction in the loop costs as much MFMA time, so it has
+// none (addresses are scalar bases plus lane offsets, LDS stages immediates).
+// 64x64x16 tiles: 1024^3 22.1 -> 20.3 us (106 TFLOP/s); 1003x1501x777 58.8 ->
+// 28.4 us (staged through registers with checked loads before).  A chunk is one k step of every MFMA block of the wave
 // (KGS k values).  The operands of chunk c + D are read while the MFMAs of
 // chunk c run, from a ring of D + 1 operand sets (D = 3 with unroll >= 16 when
 // the chunks of a K-tile divide into whole rings, else 1).  The stage barrier
@@ -378,15 +388,14 @@ constexpr bool mm_pipelined() {
 // copies are spread over the chunks before the barrier.  Past the end of the
 // split the last K-tile is loaded again into a stage nobody reads, so every
 // iteration has the same copies in flight and the wait counts are constants.
-template <int WM, int WN, int BK, int UF, int DB, int KG, class Acc, int MB, int NB>
+template <int WM, int WN, int BK, int UF, int DB, int KG, int W, class Acc, int MB, int NB>
 __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0, int kt0, int kt1,
                                              float *smem, Acc (&acc)[MB][NB]) {
     using S = MfmaShape<WM, WN, BK, KG>;
     constexpr int BM = 2 * WM, BN = 2 * WN, NT = 256 * KG;
     constexpr int ST = mm_stages(BM, BN, BK, DB);
     constexpr int STAGE = BM * BK + BK * BN;
-    constexpr int SPR = BK / 4, A4 = BM * SPR, B4 = BK * BN / 4;
-    constexpr int AL = A4 / NT, BL = B4 / NT, L = AL + BL;
+    constexpr int AL = BM * BK / W / NT, BL = BK * BN / W / NT, L = AL + BL;
     constexpr int IM = S::IM, VEC = S::VEC, KGS = S::KGS, NCH = S::NCH;
     constexpr int D = UF >= 16 && NCH % 4 == 0 ? 3 : 1;
     constexpr int RG = D + 1;
@@ -401,31 +410,56 @@ __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0
     const int wr = wq >> 1, wc = wq & 1;
     const int li = lane % IM, lg = lane / IM;
 
-    // per-thread sources of K-tile 0; a tile adds kt*BK (A) or kt*BK*N (B)
-    const float *pa[AL], *pb[BL];
+    // Copy j's position in the stage is (j * NT + thread) * W, its source row r of
+    // A at k (slot permuted) or row k of B at column c; both from a base that
+    // moves with the K-tile.
+    auto a_src = [&](int j, int &row, int &k) {
+        const int p = (j * NT + tid) * W;
+        row = p / BK;
+        k = ((((p % BK) >> 2) ^ a_swz<BK>(row)) << 2) + p % 4;
+    };
+    unsigned oa[AL], ob[BL];
 #pragma unroll
     for (int j = 0; j < AL; ++j) {
-        const int c = j * NT + wid * 64 + lane;
-        const int row = c / SPR, slot = c % SPR;
-        pa[j] = a.A + (size_t)(m0 + row) * a.K + 4 * (slot ^ a_swz<BK>(row));
+        int row, k;
+        a_src(j, row, k);
+        row = min(m0 + row, a.M - 1);
+        oa[j] = 4u * (unsigned(row - m0) * unsigned(a.K) + k);
     }
 #pragma unroll
     for (int j = 0; j < BL; ++j) {
-        const int c = j * NT + wid * 64 + lane;
-        const int k = c / (BN / 4), n4 = c % (BN / 4);
-        pb[j] = a.B + (size_t)k * a.N + n0 + 4 * n4;
+        const int p = (j * NT + tid) * W, k = p / BN, c = min(n0 + p % BN, a.N - W);
+        ob[j] = 4u * (unsigned(k) * unsigned(a.N) + c);
     }
-    // copy j of K-tile kt into the stage at st (the LDS slot is wave-uniform)
-    auto copy = [&](int kt, float *st, int j) {
-        if (j < AL) {
-            __builtin_amdgcn_global_load_lds(DS_GLOBAL(pa[j] + (size_t)kt * BK),
-                                             DS_LOCAL(st + (j * NT + wsc * 64) * 4), 16, 0, 0);
-        } else {
-            const int jb = j - AL;
-            __builtin_amdgcn_global_load_lds(DS_GLOBAL(pb[jb] + (size_t)kt * BK * a.N),
-                                             DS_LOCAL(st + BM * BK + (jb * NT + wsc * 64) * 4), 16,
-                                             0, 0);
+    const float *abase = a.A + (size_t)m0 * a.K;
+    // copy j of K-tile kt into the stage at st (the LDS slot is wave-uniform);
+    // TAIL: the tile may reach past K
+    auto copy = [&]<bool TAIL>(std::bool_constant<TAIL>, int kt, float *st, int j) {
+        const bool isa = j < AL;
+        const int jb = j - AL;
+        float *dst = st + (isa ? 0 : BM * BK) + ((isa ? j : jb) * NT + wsc * 64) * W;
+        if constexpr (TAIL) {
+            int row, k;
+            if (isa) a_src(j, row, k);
+            else k = (jb * NT + tid) * W / BN;
+            if (kt * BK + k >= a.K) {
+#pragma unroll
+                for (int v = 0; v < W; ++v) dst[lane * W + v] = 0.f;
+                return;
+            }
         }
+        const char *base = reinterpret_cast<const char *>(isa ? abase + (size_t)kt * BK
+                                                              : a.B + (size_t)kt * BK * a.N);
+        // scalar base plus 32-bit lane offset is an address form of the copy; with
+        // either out of sight (summed or widened before the loop) each copy takes a
+        // 64-bit vector addition
+        __asm__("" : "+s"(base));
+        unsigned &o = isa ? oa[isa ? j : 0] : ob[isa ? 0 : jb];
+        __asm__ volatile("" : "+v"(o));
+        if constexpr (W == 4)
+            __builtin_amdgcn_global_load_lds(DS_GLOBAL(base + o), DS_LOCAL(dst), 16, 0, 0);
+        else
+            __builtin_amdgcn_global_load_lds(DS_GLOBAL(base + o), DS_LOCAL(dst), 4, 0, 0);
     };
 
     struct Ops {
@@ -433,7 +467,7 @@ __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0
         float b[VEC][NB];
     };
     const int arow = wr * WM + li;
-    const int bcol = BM * BK + wc * WN + li;
+    const int brow = BM * BK + wc * WN + li + (kg * S::KR + VEC * lg) * BN;
     auto read = [&](const float *st, int c, Ops &o) {
         const int k = kg * S::KR + c * KGS + VEC * lg;
 #pragma unroll
@@ -456,7 +490,7 @@ __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
 #pragma unroll
-            for (int j = 0; j < NB; ++j) o.b[v][j] = st[bcol + (k + v) * BN + j * IM];
+            for (int j = 0; j < NB; ++j) o.b[v][j] = st[brow + (c * KGS + v) * BN + j * IM];
     };
     auto mma = [&](const Ops &o) {
 #pragma unroll
@@ -483,28 +517,35 @@ __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0
         }
     };
 
+    // A K-tile that reaches past K is the last of the last split: the iterations
+    // whose copies may touch it (and a prologue that does) take the checked copies,
+    // some lanes of which issue nothing, so they wait for every copy in flight.
+    const bool tail = kt1 == a.nkt && a.K % BK != 0;
+    const int kmain = tail ? max(kt0, kt1 - ST) : kt1;
     // prologue: K-tiles kt0 .. kt0+ST-2, then wait for the first
 #pragma unroll
     for (int p = 0; p < ST - 1; ++p)
 #pragma unroll
-        for (int j = 0; j < L; ++j) copy(min(kt0 + p, kt1 - 1), smem + p * STAGE, j);
-    stage_barrier<L * (ST - 2)>();
+        for (int j = 0; j < L; ++j) {
+            const int kt = min(kt0 + p, kt1 - 1);
+            if (tail && kt == kt1 - 1) copy(std::true_type{}, kt, smem + p * STAGE, j);
+            else copy(std::false_type{}, kt, smem + p * STAGE, j);
+        }
+    if (tail) stage_barrier<0>();
+    else stage_barrier<L * (ST - 2)>();
     Ops o[RG];
 #pragma unroll
     for (int c = 0; c < D; ++c) read(smem, c, o[c]);
 
-    int s = 0;
-    for (int kt = kt0; kt < kt1; ++kt) {
-        int sp = s + ST - 1;
-        if (sp >= ST) sp -= ST;
-        int sn = s + 1;
-        if (sn == ST) sn = 0;
+    // K-tile kt in stage s
+    auto tile = [&]<bool TAIL>(std::bool_constant<TAIL> t, int kt, int s) {
+        const int sp = s == 0 ? ST - 1 : s - 1, sn = s == ST - 1 ? 0 : s + 1;
         const float *cur = smem + s * STAGE, *nxt = smem + sn * STAGE;
         float *fill = smem + sp * STAGE;
         const int ktf = min(kt + ST - 1, kt1 - 1);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            if (c == PRE) stage_barrier<L * (ST - 2)>();
+            if (c == PRE) stage_barrier<TAIL ? 0 : L * (ST - 2)>();
             Ops &rd = RING ? o[(c + D) % RG] : o[D];
             if (c + D < NCH) read(cur, c + D, rd);
             else read(nxt, c + D - NCH, rd);
@@ -512,7 +553,7 @@ __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0
             if (c < PRE) {
 #pragma unroll
                 for (int q = 0; q < PER; ++q)
-                    if (c * PER + q < L) copy(ktf, fill, c * PER + q);
+                    if (c * PER + q < L) copy(t, ktf, fill, c * PER + q);
             }
             interleave();
             if constexpr (!RING) {
@@ -520,7 +561,21 @@ __device__ __forceinline__ void mm_mfma_pipe(const MatmulArgs &a, int m0, int n0
                 for (int r = 0; r < D; ++r) o[r] = o[r + 1];
             }
         }
-        s = sn;
+    };
+    int kt = kt0, s = 0;
+    // Small tiles run the stages of the ring unrolled: their LDS addresses are
+    // immediates then (an fp32 MFMA holds the vector unit an addition needs).
+    if constexpr (NCH * VEC * MB * NB <= 32)
+        for (; kt + ST <= kmain; kt += ST)
+#pragma unroll
+            for (int q = 0; q < ST; ++q) tile(std::false_type{}, kt + q, q);
+    for (; kt < kmain; ++kt) {
+        tile(std::false_type{}, kt, s);
+        if (++s == ST) s = 0;
+    }
+    for (; kt < kt1; ++kt) {
+        tile(std::true_type{}, kt, s);
+        if (++s == ST) s = 0;
     }
     // the reloads past the end are still in flight
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -600,12 +655,16 @@ __global__ __launch_bounds__(256 * KG) void mm_mfma(MatmulArgs a) {
             }
         }
     };
-    if constexpr (mm_pipelined<WM, WN, BK, DB, KG>()) {
-        if (a.direct) mm_mfma_pipe<WM, WN, BK, UF, DB, KG>(a, m0, n0, kt0, kt1, smem, acc);
-        else k_loop<BM, BN, BK, ST, 256 * KG>(a, m0, n0, kt0, kt1, smem, compute);
-    } else {
-        k_loop<BM, BN, BK, ST, 256 * KG>(a, m0, n0, kt0, kt1, smem, compute);
+    constexpr bool P4 = mm_pipelined<WM, WN, BK, DB, KG, 4>(),
+                   P1 = mm_pipelined<WM, WN, BK, DB, KG, 1>();
+    if constexpr (P4) {
+        if (a.pipe == 4) mm_mfma_pipe<WM, WN, BK, UF, DB, KG, 4>(a, m0, n0, kt0, kt1, smem, acc);
     }
+    if constexpr (P1) {
+        if (a.pipe == 1) mm_mfma_pipe<WM, WN, BK, UF, DB, KG, 1>(a, m0, n0, kt0, kt1, smem, acc);
+    }
+    if (!(P4 && a.pipe == 4) && !(P1 && a.pipe == 1))
+        k_loop<BM, BN, BK, ST, 256 * KG>(a, m0, n0, kt0, kt1, smem, compute);
 
     constexpr int NV = BIG ? 16 : 4;
     if constexpr (KG > 1) {
