@@ -91,9 +91,12 @@ FAMILY_NAME = {1: "conv_valu", 2: "conv_mfma", 3: "mm_valu", 4: "mm_mfma", 5: "c
 def kernel_name(space, idx):
     """Template instance the schedule selects (as rocprofv3 lists it)."""
     info = space.kernel_info(idx)
-    if info["family"] == 5 and info["nparams"] == 6:
-        return f"conv_split<{info['params'][0] // 2}, {info['params'][1] // 2}>"
-    args = ", ".join(str(v) for v in info["params"][: info["nparams"]])
+    params = info["params"][: info["nparams"]]
+    if info["family"] == 5:
+        if params[5:] == [1]:
+            return f"conv_split<{params[0] // 2}, {params[1] // 2}>"
+        params = (params + [0])[:6]      # filter size of the build, 0: any
+    args = ", ".join(str(v) for v in params)
     return f"{FAMILY_NAME[info['family']]}<{args}>"
 
 

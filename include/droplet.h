@@ -180,7 +180,8 @@ enum {
     DS_KERNEL_MM_VALU = 3,    /* mm_valu<RM, RN, BK, UF, DB> */
     DS_KERNEL_MM_MFMA = 4,    /* mm_mfma<WM, WN, BK, UF, DB, KG> */
     DS_KERNEL_CONV_MFMA2 = 5  /* conv_mfma2<TKB, NPB, U, KG, RC> (conv mfma = 2 and 3); with
-                                 a sixth parameter of 1, conv_split<TKB / 2, NPB / 2> */
+                                 a sixth parameter of 3 or 5, its build for filters of that
+                                 size, and of 1, conv_split<TKB / 2, NPB / 2> */
 };
 
 /* The compiled program a valid schedule selects (Definition 1: an annotated

@@ -201,6 +201,14 @@ constexpr bool conv2_regs_ok(int tkb, int npb, int kg) {
            tkb + npb <= (kg == 4 ? 8 : kg == 2 ? 12 : 20);
 }
 
+// Whether an instance has builds for FS x FS filters, 3 or 5 (kern_conv.hip): up
+// to eight blocks a wave (four for 5x5) that do not spill at two waves per SIMD,
+// or at the four a 1024-thread workgroup needs.
+constexpr bool conv2_rows(int tkb, int npb, int u, int kg, int rc, int fs) {
+    return (fs == 3 || fs == 5) && tkb * npb <= (fs == 3 ? 8 : 4) && !(npb == 8 && u > 1) &&
+           !(kg == 4 && rc != kConv2FewCopies && u == 4 && tkb * npb == 4);
+}
+
 // Copy units of conv_mfma2 for its copy widths (vw, vh) and thread count.
 inline void conv2_units(Conv2Args &a, int threads) {
     const int tc4 = 4 * a.t4;
@@ -426,6 +434,7 @@ int launch_plan(const Plan &plan, hipStream_t stream);
 const void *conv_valu_instance(int kpt, int ppt, int uf, int lds);
 const void *conv_mfma_instance(int tkb, int npb, int d, int lds);
 const void *conv_mfma2_instance(int tkb, int npb, int u, int kg, int rc);
+const void *conv_rows_instance(int tkb, int npb, int u, int kg, int rc, int fs);
 const void *conv_split_instance(int tkb, int npb);
 const void *mm_valu_instance(int rm, int rn, int bk, int uf, int dbuf);
 const void *mm_mfma_instance(int wm, int wn, int bk, int uf, int dbuf, int kg);

@@ -21,6 +21,7 @@ const Space &space_of(const ds_space *s);
 const void *g_conv_valu[kConvValuSlots];
 const void *g_conv_mfma[kConvMfmaSlots];
 const void *g_conv_mfma2[kConvMfma2Slots];
+const void *g_conv_rows[2 * kConvMfma2Slots];
 const void *g_conv_split[kConvSplitSlots];
 const void *g_mm_valu[kMmValuSlots];
 const void *g_mm_mfma[kMmMfmaSlots];
@@ -429,6 +430,13 @@ const void *conv_mfma2_instance(int tkb, int npb, int u, int kg, int rc) {
     return g_conv_mfma2[(((a * 6 + b) * 3 + c) * 3 + d) * 2 + (rc == kConv2FewCopies)];
 }
 
+const void *conv_rows_instance(int tkb, int npb, int u, int kg, int rc, int fs) {
+    if (!conv2_rows(tkb, npb, u, kg, rc, fs) || !conv_mfma2_instance(tkb, npb, u, kg, rc)) return nullptr;
+    const int slot = (((log2_exact(tkb) * 6 + log2_exact(npb)) * 3 + log2_exact(u)) * 3 +
+                      log2_exact(kg)) * 2 + (rc == kConv2FewCopies);
+    return g_conv_rows[(fs == 5 ? kConvMfma2Slots : 0) + slot];
+}
+
 const void *conv_split_instance(int tkb, int npb) {
     const int a = log2_exact(tkb) - 1, b = log2_exact(npb) - 1;
     return a < 0 || a > 1 || b < 0 || b > 1 ? nullptr : g_conv_split[a * 2 + b];
@@ -455,6 +463,7 @@ int count_instances() {
     for (auto p : g_conv_valu) n += p != nullptr;
     for (auto p : g_conv_mfma) n += p != nullptr;
     for (auto p : g_conv_mfma2) n += p != nullptr;
+    for (auto p : g_conv_rows) n += p != nullptr;
     for (auto p : g_conv_split) n += p != nullptr;
     for (auto p : g_mm_valu) n += p != nullptr;
     for (auto p : g_mm_mfma) n += p != nullptr;
@@ -507,7 +516,7 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         plan.func = conv_mfma2_instance(c.tkb, c.npb, c.u, c.kg, a.rc);
         plan.family = DS_KERNEL_CONV_MFMA2;
         plan.nparams = 5;
-        const int pr[6] = {c.tkb, c.npb, c.u, c.kg, a.rc, 1};
+        const int pr[6] = {c.tkb, c.npb, c.u, c.kg, a.rc, 0};
         std::memcpy(plan.params, pr, sizeof pr);
         plan.slot = (((log2_exact(c.tkb) * 6 + log2_exact(c.npb)) * 3 + log2_exact(c.u)) * 3 +
                      log2_exact(c.kg)) * 2 + (a.rc == kConv2FewCopies);
@@ -515,8 +524,14 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         if (conv2_split_setup(a, c, &lds)) {
             plan.func = conv_split_instance(c.tkb, c.npb);
             plan.nparams = 6;
+            plan.params[5] = 1;
             plan.slot = kConvMfma2Slots + (log2_exact(c.tkb) - 1) * 2 + log2_exact(c.npb) - 1;
             plan.lds = int(lds);
+        } else if (a.R == a.S && conv_rows_instance(c.tkb, c.npb, c.u, c.kg, a.rc, a.S)) {
+            plan.func = conv_rows_instance(c.tkb, c.npb, c.u, c.kg, a.rc, a.S);
+            plan.nparams = 6;
+            plan.params[5] = a.S;
+            plan.slot += kConvSplitSlots + kConvMfma2Slots * (a.S == 3 ? 1 : 2);
         }
         plan.splits = a.ksw > 1 ? int(cdiv64(a.chunks, a.cps)) : 1;
         plan.y_elems = int64_t(a.N) * a.K * a.P * a.Q;

@@ -818,11 +818,11 @@ constexpr int kConv2Waves2[] = {
 constexpr int kConv2FewWaves6[] = {
     10111, 10112, 10114, 10121, 10122, 10124, 10141, 10142, 10144, 10211, 10212, 10214,
     10221, 10222, 10224, 10241, 10242, 10244, 10411, 10412, 10414, 10421, 10422, 10424,
-    20111, 20112, 20114, 20141, 20142, 20144, 20211, 20212, 20214,
+    20111, 20112, 20114, 20121, 20122, 20124, 20141, 20142, 20144, 20211, 20212, 20214,
     20221, 20222, 20224, 20241, 20242, 20244, 40111, 40112, 40114, 40121, 40122, 40124,
     40141, 40142, 40144, 40211, 40212};
 constexpr int kConv2FewWaves5[] = {
-    10441, 10442, 10444, 10811, 10812, 20121, 20122, 20124, 20411, 20412};
+    10441, 10442, 10444, 10811, 10812, 20411, 20412};
 constexpr int kConv2FewWaves4[] = {
     40221, 40222, 40411, 40412};
 constexpr int kConv2FewWaves3[] = {
@@ -854,19 +854,32 @@ constexpr int conv2_waves(int tkb, int npb, int u, int kg, int rc) {
     return 1;
 }
 
-// Instances with the row-wise loops: the small tiles, whose steps have few MFMAs
-// beside their address arithmetic (one MFMA against 2.5 vector and 5 scalar
-// instructions in <1, 1, 4, 4>, now 0.5 and 0.6).  Larger ones spill under their
-// launch bounds with the addresses those loops hold.  Measured: 5x5 over 37
-// channels, batch 3, 61x53 (<1, 2, 1, 1>) 69.0 -> 47.7 us; ResNet-50's 3x3 stride
-// 2 over 512 channels at batch 1 (<2, 1, 1, 2>) 15.9 -> 14.9; 3x3 over 64
-// channels, 56x56 (<1, 1, 4, 4>) 9.74 -> 9.38.
-constexpr bool conv2_rows(int tkb, int npb, int u) {
-    return tkb * npb <= 2 && u * tkb * npb <= 4;
+// 3x3 and 5x5 filters have instances of their own (FS; conv2_rows) for tiles of up
+// to eight blocks a wave (four for 5x5): a step of a small tile spends more issue
+// slots on its addresses (one vector addition per operand read, which holds off
+// fp32 MFMAs, and two divisions; <1, 1, 4, 4>: 2.5 vector and 5 scalar
+// instructions an MFMA, now 0.5 and 0.6) than on its MFMAs.  142 sampled 3x3 and
+// 5x5 points of six shapes ran 1.18 times as fast (geometric mean; none slower,
+// the best 1.8): 5x5 over 37 channels, batch 3, 61x53 (<1, 2, 1, 1>) 69.0 -> 47.7
+// us; ResNet-50's 3x3 stride 2 over 512 channels at batch 1 (<2, 1, 1, 2>) 15.9 ->
+// 14.9; 3x3 over 64 channels, 56x56 (<1, 1, 4, 4>) 9.74 -> 9.38.  1x1 filters, a
+// row a step, ran 5 to 15% slower this way, and as much slower in kernels that
+// only hold such a loop beside their own: hence builds apart.
+// Their waves per SIMD: the most at which no instance of a row spills, found by
+// compiling each under every bound (few: the 4-copy builds).
+constexpr int conv2_row_waves(int tkb, int npb, int u, int rc) {
+    const int blocks = tkb * npb;
+    const bool few = rc == kConv2FewCopies;
+    if (blocks == 1) return few || u < 4 ? 6 : 5;
+    if (blocks == 2) return few ? (u == 4 && npb == 2 ? 5 : 6) : u < 4 ? 5 : 4;
+    if (blocks == 4) return few ? (u == 1 ? 6 : u == 2 ? 5 : 4) : u == 1 || (u == 2 && tkb < 4) ? 4 : 3;
+    return few ? (u < 4 ? 4 : 3) : u < 4 ? 3 : 2;
 }
 
-template <int TKB, int NPB, int U, int KG, int RC>
-__global__ __launch_bounds__(256 * KG, conv2_waves(TKB, NPB, U, KG, RC)) void conv_mfma2(Conv2Args a) {
+template <int TKB, int NPB, int U, int KG, int RC, int FS>
+__global__ __launch_bounds__(256 * KG, FS ? conv2_row_waves(TKB, NPB, U, RC)
+                                          : conv2_waves(TKB, NPB, U, KG, RC)) void
+conv_mfma2(Conv2Args a) {
     extern __shared__ float smem[];
     using q4::fdv;
     // tile of this workgroup (tile order: k, q, p, split, image)
@@ -1106,13 +1119,11 @@ __global__ __launch_bounds__(256 * KG, conv2_waves(TKB, NPB, U, KG, RC)) void co
                     }
         };
         Ops o[2];
-        // The steps of an S x S filter, a row of S taps at a time: the taps of a
-        // row are immediate offsets from one LDS address per operand block, moved
-        // on once a row.  An fp32 MFMA holds the vector unit, so the addition per
-        // operand read that steps of any filter need costs MFMA time, and their
-        // divisions outweigh a small tile's MFMAs.
-        auto rows = [&]<int S>(std::integral_constant<int, S>) {
-            constexpr int SA = 4 * KG * S * S;             // floats per quad step of A
+        if constexpr (FS > 0) {
+            // The steps of an FS x FS filter, a row of taps at a time: the taps of a
+            // row are immediate offsets from one LDS address per operand block,
+            // moved on once a row.
+            constexpr int S = FS, SA = 4 * KG * S * S;             // floats per quad step of A
             const int nrow = (a.t4 / (KG * U)) * S;
             int pa[TKB], pb[U][NPB];
 #pragma unroll
@@ -1160,8 +1171,7 @@ __global__ __launch_bounds__(256 * KG, conv2_waves(TKB, NPB, U, KG, RC)) void co
                 row(std::integral_constant<int, 1>{});
             }
             if (left > 0) row(std::integral_constant<int, 0>{});
-        };
-        auto steps = [&]() {
+        } else {
             load(0, o[0]);
             int j = 0;
             for (; j + 2 <= tg; j += 2) {
@@ -1171,15 +1181,6 @@ __global__ __launch_bounds__(256 * KG, conv2_waves(TKB, NPB, U, KG, RC)) void co
                 mma(o[1]);
             }
             if (j < tg) mma(o[0]);
-        };
-        if constexpr (conv2_rows(TKB, NPB, U)) {
-            const int sq = a.R == a.S ? a.S : 0;
-            if (sq == 3) rows(std::integral_constant<int, 3>{});
-            else if (sq == 1) rows(std::integral_constant<int, 1>{});
-            else if (sq == 5) rows(std::integral_constant<int, 5>{});
-            else steps();
-        } else {
-            steps();
         }
     }
 
@@ -1280,6 +1281,7 @@ constexpr int kMfmaSlots = kConvMfmaSlots;
 extern const void *g_conv_valu[kConvValuSlots];
 extern const void *g_conv_mfma[kConvMfmaSlots];
 extern const void *g_conv_mfma2[kConvMfma2Slots];
+extern const void *g_conv_rows[2 * kConvMfma2Slots];
 
 #ifndef DS_SLICE
 #define DS_SLICE 0
@@ -1312,7 +1314,12 @@ void reg_mfma2() {
     constexpr int TKB = 1 << itkb, NPB = 1 << inpb, U = 1 << iu, KG = 1 << ikg;
     constexpr int RC = few ? kConv2FewCopies : kConv2MaxCopies;
     if constexpr (conv2_regs_ok(TKB, NPB, KG) && I % DS_NSLICES == DS_SLICE)
-        g_conv_mfma2[I] = reinterpret_cast<const void *>(&conv_mfma2<TKB, NPB, U, KG, RC>);
+        g_conv_mfma2[I] = reinterpret_cast<const void *>(&conv_mfma2<TKB, NPB, U, KG, RC, 0>);
+    if constexpr (conv2_regs_ok(TKB, NPB, KG) && conv2_rows(TKB, NPB, U, KG, RC, 3) && I % DS_NSLICES == DS_SLICE)
+        g_conv_rows[I] = reinterpret_cast<const void *>(&conv_mfma2<TKB, NPB, U, KG, RC, 3>);
+    if constexpr (conv2_regs_ok(TKB, NPB, KG) && conv2_rows(TKB, NPB, U, KG, RC, 5) && I % DS_NSLICES == DS_SLICE)
+        g_conv_rows[kConvMfma2Slots + I] =
+            reinterpret_cast<const void *>(&conv_mfma2<TKB, NPB, U, KG, RC, 5>);
 }
 
 template <size_t... I>

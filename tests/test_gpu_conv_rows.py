@@ -1,6 +1,6 @@
-"""The row-wise loops of the channel-quad conv's small tiles on the GPU: 1x1, 3x3
-and 5x5 filters against the step-by-step loop's filters (1x3, 7x7), odd and even
-numbers of quad blocks per chunk, ragged channels.  Small-integer inputs, so
+"""The row-wise loops of the channel-quad conv's small tiles on the GPU: 3x3 and
+5x5 filters beside the step-by-step loop's (1x1, 1x3, 7x7), odd and even numbers
+of quad blocks per chunk, ragged channels.  Small-integer inputs, so
 every output must equal the oracle's."""
 import numpy as np
 import pytest

@@ -62,8 +62,8 @@ def points(L, sh, knobs):
             for vec in (4, 1):
                 f32 = space.sched([vals.index(v) if v in vals else -1 for vals, v in zip(
                     space.values, dict(kn, tc=ch, unroll=unroll, vec=vec).values())])
-                if -1 not in f32.index() and space.valid(f32.index()) and len(
-                        space.kernel_info(f32.index())["params"]) == 5:
+                if -1 not in f32.index() and space.valid(f32.index()) and (
+                        space.kernel_info(f32.index())["params"][5:] != [1]):
                     return space, split, f32
     raise AssertionError(sh)
 
