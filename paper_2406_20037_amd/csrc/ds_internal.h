@@ -120,8 +120,8 @@ struct MatmulArgs {
     int vecA, vecB;       // 1: 16-byte loads along K of A / along N of B are legal
     int direct;           // 1: every tile is full and aligned: K-tiles go straight to LDS
     int pipe;             // floats per lane of the pipelined MFMA loop's copies: 4 when rows
-                          //    of A and B are whole aligned 16-byte groups, else 1 (0: a
-                          //    tile's 32-bit offsets do not reach; staged through registers)
+                          //    of A and B are whole aligned 16-byte groups, else 1 (0:
+                          //    staged through registers)
     float *part;          // ks > 1: split z writes its partial C at part + z * M*N
     int gm;               // tile rows per group of the XCD tile order (mm_group_rows)
 };
