@@ -92,6 +92,8 @@ def kernel_name(space, idx):
     """Template instance the schedule selects (as rocprofv3 lists it)."""
     info = space.kernel_info(idx)
     params = info["params"][: info["nparams"]]
+    if info["family"] == 3 and len(params) == 6:
+        return f"mm_rows<{params[5]}>"
     if info["family"] == 5:
         if params[5:] == [1]:
             return f"conv_split<{params[0] // 2}, {params[1] // 2}>"
@@ -178,7 +180,7 @@ class Workload:
             m = L.ds_measure(res.best, io, final_cfg)
             task.update(best=res.best, res=res, meas=m,
                         knobs=task["space"].knobs(res.best),
-                        geom=task["space"].geometry(res.best.index()))
+                        info=task["space"].kernel_info(res.best.index()))
             task["kernel"] = kernel_name(task["space"], res.best.index())
             log(f"tuned {self.name}/{task['name']}: {task['knobs']} {m.median_ms * 1e3:.2f} us "
                 f"({task['flops'] / (m.median_ms * 1e-3) / 1e9:.0f} GFLOP/s), explored "
@@ -389,7 +391,7 @@ def main(argv=None):
     roofline.update({"traffic": traffic,
                      "kernel": task["kernel"], "task": task["name"],
                      "schedule": task["knobs"],
-                     "grid_threads": int(task["geom"]["grid"]) * int(task["geom"]["threads"]),
+                     "grid_threads": int(task["info"]["grid"]) * int(task["info"]["threads"]),
                      "avg_launch_us": round(avg_ms * 1e3, 3),
                      "algorithmic_flops": task["flops"], "algorithmic_bytes": task["bytes"]})
 

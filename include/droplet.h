@@ -144,7 +144,7 @@ int sched_origin(const ds_space *space, ds_sched *out);
 typedef struct {
     int32_t valid;
     int32_t threads;      /* workgroup size */
-    int64_t grid;         /* number of workgroups (1-D) */
+    int64_t grid;         /* number of workgroups (1-D; mm_rows launches its own shape) */
     int32_t lds_bytes;    /* dynamic LDS per workgroup (a split-operand launch uses its
                              own layout: ds_kernel_info.lds_bytes) */
     int32_t acc;          /* fp32 accumulators per lane */
@@ -177,7 +177,8 @@ int sched_has_kernel(const ds_space *space, const ds_sched *s);
 enum {
     DS_KERNEL_CONV_VALU = 1,  /* conv_valu<KPT, PPT, UF, LDS> */
     DS_KERNEL_CONV_MFMA = 2,  /* conv_mfma<TKB, NPB, D, LDS> (conv mfma = 1) */
-    DS_KERNEL_MM_VALU = 3,    /* mm_valu<RM, RN, BK, UF, DB> */
+    DS_KERNEL_MM_VALU = 3,    /* mm_valu<RM, RN, BK, UF, DB>; with a sixth parameter,
+                                 mm_rows<that> */
     DS_KERNEL_MM_MFMA = 4,    /* mm_mfma<WM, WN, BK, UF, DB, KG> */
     DS_KERNEL_CONV_MFMA2 = 5  /* conv_mfma2<TKB, NPB, U, KG, RC> (conv mfma = 2 and 3); with
                                  a sixth parameter of 3 or 5, its build for filters of that

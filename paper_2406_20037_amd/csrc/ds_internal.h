@@ -122,6 +122,7 @@ struct MatmulArgs {
     int pipe;             // floats per lane of the pipelined MFMA loop's copies: 4 when rows
                           //    of A and B are whole aligned 16-byte groups, else 1 (0:
                           //    staged through registers)
+    int uf;               // mm_rows: unroll factor of the reduction loop
     float *part;          // ks > 1: split z writes its partial C at part + z * M*N
     int gm;               // tile rows per group of the XCD tile order (mm_group_rows)
 };
@@ -405,6 +406,18 @@ inline int mm_group_rows(int tiles_m, int tiles_n, int ks, int bm, int bn) {
         }
     }
     return best;
+}
+
+// Whether a VALU matmul point runs as mm_rows: up to four rows, tiles of 16
+// columns, a split, K-tiles of at least a pass of its threads over 32 rows, their
+// loads ahead of their use (dbuf), and rows of B in aligned 16-byte groups (K
+// below 2^30: the kernel's row index stays in an int).
+// Wider tiles keep the tiled kernel: with few of them a workgroup per 16 columns
+// is another grid than the one the point asks for.
+inline bool mm_few_rows(int64_t M, int64_t K, int mfma, int bn, int bk, int ks, int dbuf,
+                        int vecB) {
+    return !mfma && M >= 1 && M <= 4 && bn == 16 && bk >= 32 && ks >= 2 && dbuf && vecB &&
+           K < (int64_t(1) << 30);
 }
 
 struct Plan {

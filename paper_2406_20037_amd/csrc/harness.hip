@@ -23,6 +23,7 @@ const void *g_conv_mfma[kConvMfmaSlots];
 const void *g_conv_mfma2[kConvMfma2Slots];
 const void *g_conv_rows[2 * kConvMfma2Slots];
 const void *g_conv_split[kConvSplitSlots];
+const void *g_mm_rows[3];
 const void *g_mm_valu[kMmValuSlots];
 const void *g_mm_mfma[kMmMfmaSlots];
 
@@ -465,6 +466,7 @@ int count_instances() {
     for (auto p : g_conv_mfma2) n += p != nullptr;
     for (auto p : g_conv_rows) n += p != nullptr;
     for (auto p : g_conv_split) n += p != nullptr;
+    for (auto p : g_mm_rows) n += p != nullptr;
     for (auto p : g_mm_valu) n += p != nullptr;
     for (auto p : g_mm_mfma) n += p != nullptr;
     return n;
@@ -625,7 +627,7 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
                          : mm_valu_instance(g.t0, g.t1, bk, g.unroll_eff, dbuf);
         plan.family = mfma ? DS_KERNEL_MM_MFMA : DS_KERNEL_MM_VALU;
         plan.nparams = mfma ? 6 : 5;
-        const int pr[6] = {g.t0, g.t1, bk, g.unroll_eff, dbuf, kg};
+        const int pr[6] = {g.t0, g.t1, bk, g.unroll_eff, dbuf, mfma ? kg : 0};
         std::memcpy(plan.params, pr, sizeof pr);
         const int lb = log2_exact(bk) - 2, lu = log2_exact(g.unroll_eff);
         plan.slot = mfma ? ((((log2_exact(g.t0) - 4) * 4 + (log2_exact(g.t1) - 4)) * 5 + lb) * 7 + lu) *
@@ -633,6 +635,18 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
                          : (((log2_exact(g.t0) * 5 + log2_exact(g.t1)) * 5 + lb) * 7 + lu) * 2 + dbuf;
         plan.splits = a.ks > 1 ? int(cdiv64(a.nkt, a.kps)) : 1;
         plan.y_elems = int64_t(a.M) * a.N;
+        if (mm_few_rows(a.M, a.K, mfma, bn, bk, a.ks, dbuf, a.vecB)) {
+            const int lr = a.M > 2 ? 2 : a.M - 1;
+            a.uf = g.unroll_eff;
+            plan.func = g_mm_rows[lr];
+            plan.nparams = 6;
+            plan.params[5] = 1 << lr;
+            plan.slot = kMmValuSlots + lr;
+            plan.threads = 128 * a.ks;
+            plan.grid = a.tiles_n;
+            plan.lds = 0;
+            plan.splits = 1;
+        }
     }
     if (!plan.func) {
         set_error("no compiled kernel instance for this schedule");
