@@ -97,6 +97,8 @@ def kernel_name(space, idx):
     if info["family"] == 5:
         if params[5:] == [1]:
             return f"conv_split<{params[0] // 2}, {params[1] // 2}>"
+        if params[5:] == [2]:
+            return f"conv_few<{params[0]}, {params[1]}>"
         params = (params + [0])[:6]      # filter size of the build, 0: any
     args = ", ".join(str(v) for v in params)
     return f"{FAMILY_NAME[info['family']]}<{args}>"

@@ -145,8 +145,8 @@ typedef struct {
     int32_t valid;
     int32_t threads;      /* workgroup size */
     int64_t grid;         /* number of workgroups (1-D; mm_rows launches its own shape) */
-    int32_t lds_bytes;    /* dynamic LDS per workgroup (a split-operand launch uses its
-                             own layout: ds_kernel_info.lds_bytes) */
+    int32_t lds_bytes;    /* dynamic LDS per workgroup (split-operand launches and those of
+                             up to three channels use their own: ds_kernel_info.lds_bytes) */
     int32_t acc;          /* fp32 accumulators per lane */
     int32_t unroll_eff;   /* unroll factor of the reduction loop (conv MFMA: the
                              number of 16-step groups read ahead, 1..3) */
@@ -182,7 +182,8 @@ enum {
     DS_KERNEL_MM_MFMA = 4,    /* mm_mfma<WM, WN, BK, UF, DB, KG> */
     DS_KERNEL_CONV_MFMA2 = 5  /* conv_mfma2<TKB, NPB, U, KG, RC> (conv mfma = 2 and 3); with
                                  a sixth parameter of 3 or 5, its build for filters of that
-                                 size, and of 1, conv_split<TKB / 2, NPB / 2> */
+                                 size, of 1, conv_split<TKB / 2, NPB / 2>, and of 2,
+                                 conv_few<TKB, NPB> */
 };
 
 /* The compiled program a valid schedule selects (Definition 1: an annotated

@@ -23,6 +23,7 @@ const void *g_conv_mfma[kConvMfmaSlots];
 const void *g_conv_mfma2[kConvMfma2Slots];
 const void *g_conv_rows[2 * kConvMfma2Slots];
 const void *g_conv_split[kConvSplitSlots];
+const void *g_conv_few[kConvFewSlots];
 const void *g_mm_rows[3];
 const void *g_mm_valu[kMmValuSlots];
 const void *g_mm_mfma[kMmMfmaSlots];
@@ -443,6 +444,11 @@ const void *conv_split_instance(int tkb, int npb) {
     return a < 0 || a > 1 || b < 0 || b > 1 ? nullptr : g_conv_split[a * 2 + b];
 }
 
+const void *conv_few_instance(int tkb, int gb) {
+    const int a = log2_exact(tkb), b = log2_exact(gb);
+    return a < 0 || a > 2 || b < 0 || b > 1 ? nullptr : g_conv_few[a * 2 + b];
+}
+
 const void *mm_valu_instance(int rm, int rn, int bk, int uf, int dbuf) {
     const int a = log2_exact(rm), b = log2_exact(rn), k = log2_exact(bk) - 2, c = log2_exact(uf);
     if (a < 0 || a > 4 || b < 0 || b > 4 || k < 0 || k > 4 || c < 0 || c > 6 || (dbuf & ~1))
@@ -466,6 +472,7 @@ int count_instances() {
     for (auto p : g_conv_mfma2) n += p != nullptr;
     for (auto p : g_conv_rows) n += p != nullptr;
     for (auto p : g_conv_split) n += p != nullptr;
+    for (auto p : g_conv_few) n += p != nullptr;
     for (auto p : g_mm_rows) n += p != nullptr;
     for (auto p : g_mm_valu) n += p != nullptr;
     for (auto p : g_mm_mfma) n += p != nullptr;
@@ -529,6 +536,14 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
             plan.params[5] = 1;
             plan.slot = kConvMfma2Slots + (log2_exact(c.tkb) - 1) * 2 + log2_exact(c.npb) - 1;
             plan.lds = int(lds);
+        } else if (conv2_few(a, c)) {
+            const int gb = std::min(c.npb, 2);
+            plan.func = conv_few_instance(c.tkb, gb);
+            plan.nparams = 6;
+            plan.params[1] = gb;
+            plan.params[5] = 2;
+            plan.slot = 3 * kConvMfma2Slots + kConvSplitSlots + log2_exact(c.tkb) * 2 + log2_exact(gb);
+            plan.lds = 0;
         } else if (a.R == a.S && conv_rows_instance(c.tkb, c.npb, c.u, c.kg, a.rc, a.S)) {
             plan.func = conv_rows_instance(c.tkb, c.npb, c.u, c.kg, a.rc, a.S);
             plan.nparams = 6;

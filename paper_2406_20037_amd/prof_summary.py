@@ -23,7 +23,10 @@ COPY = "__amd_rocclr_copyBuffer"
 PKG = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = {
     "mm_": ["csrc/kern_matmul.hip", "csrc/kern_common.h", "csrc/ds_internal.h"],
-    "conv_split": ["csrc/kern_conv_split.hip", "csrc/kern_common.h", "csrc/ds_internal.h"],
+    "conv_split": ["csrc/kern_conv_split.hip", "csrc/kern_conv_tile.h", "csrc/kern_common.h",
+                   "csrc/ds_internal.h"],
+    "conv_few": ["csrc/kern_conv_few.hip", "csrc/kern_conv_tile.h", "csrc/kern_common.h",
+                 "csrc/ds_internal.h"],
     "conv_": ["csrc/kern_conv.hip", "csrc/kern_common.h", "csrc/ds_internal.h"],
     "split_reduce_kernel": ["csrc/kern_reduce.hip", "csrc/kern_reduce.h", "csrc/kern_common.h"],
 }
