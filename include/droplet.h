@@ -81,7 +81,9 @@ typedef struct ds_space ds_space;
  * band tiles may reach past the output's height or width.  3x3 points of mfma 2
  * and 3 at unroll depth 1 over whole groups of eight channels compute their
  * fp32 products as six bf16 MFMAs of operands split into three bf16 values
- * (24 bits; no less precise than the fp32 MFMA).  matmul axes: bm,
+ * (24 bits; no less precise than the fp32 MFMA).  Tiles that hold infinities, NaN
+ * or operands too small for that are computed again with fp32 MFMAs in the same
+ * launch, so the time of such a launch depends on its data.  matmul axes: bm,
  * bn {16,...,256} (kept if <= M, N), bk {4,...,64} (kept if <= K), unroll,
  * dbuf {0,1}, mfma {0,1}, ks {1,2,4,8} (kept if <= K), vec {1,4} (floats per
  * lane of the operand loads).  The

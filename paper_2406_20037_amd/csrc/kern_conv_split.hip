@@ -10,6 +10,10 @@
 // often: against fp64 the error is 0.8 of the fp32 MFMA program's (3x3 over 64
 // channels: 3.6e-7 against 4.3e-7 of the result's 2-norm).
 //
+// That holds output by output, for every finite input: a workgroup whose
+// operands or outputs lie where it would not runs its tile again on fp32 MFMAs
+// (kExact and what follows it, below).
+//
 // A workgroup computes the tile of the fp32 program (conv_mfma2): tk channels x
 // th * tw pixels, four waves of 32 TB channels x 32 NB pixels.  Its reduction
 // runs in stages of eight channels; a stage's operands sit in LDS as bf16
@@ -57,13 +61,44 @@ __device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[3]) {
     p[2] = pack_bf16(x, y);
 }
 
-// The three bf16 planes of the eight channels of a unit, 16 bytes each.
+// Where the split products are as good as fp32 ones.  The bf16 MFMA keeps
+// denormals, in its operands and its sums, so a plane holds multiples of 2^-133
+// and a sum multiples of 2^-149, as an fp32 one does.
+//   - From kExact = 2^-110 on, an operand's last bit (2^-23 of it) is at least
+//     2^-133: its planes add up to it.  Smaller ones may lose up to 2^-134.
+//   - The products of operands whose product is kWhole = 2^-100 or more have,
+//     plane by plane, no bit below 2^-149.  Those of smaller ones may lose 2^-149
+//     each.
+//   - What a term loses either way is below 2^-92 where no operand is above
+//     kLarge = 2^40.  An output of kSmall = 2^-40 or more then loses less than 2^-52
+//     of itself a term, nothing beside the rounding of its fp32 sums.
+// So a loop that meets a large operand, or leaves a small output (zero among
+// them), looks at its operands again for the first two.  The loop itself only keeps
+// their largest magnitude, one instruction a pair (14x14x512: 131.8 -> 133.0 us);
+// their smallest but zero takes three (132.0 -> 136.4 us).  Where every tile looks
+// again 64x224x224 takes 426 us, where every tile runs again 970 to 1020.
+constexpr float kLarge = 0x1p40f, kSmall = 0x1p-40f;
+// The largest and smallest of three magnitudes, NaN if any is (v_maximum3_f32).
+__device__ __forceinline__ float max3(float m, float a, float b) {
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(a), fabsf(b)), m);
+}
+__device__ __forceinline__ float min3(float m, float a, float b) {
+    return __builtin_elementwise_minimum(__builtin_elementwise_minimum(fabsf(a), fabsf(b)), m);
+}
+// Magnitudes as twice their bits less one: zero, which is exact, is the largest.
+__device__ __forceinline__ unsigned mag(float v) { return 2u * __float_as_uint(v) - 1u; }
+constexpr unsigned kExact = 2u * (unsigned(127 - 110) << 23) - 1u;
+constexpr unsigned kWhole = 2 * 127 - 100;   // sum of the biased exponents
+
+// The three bf16 planes of the eight channels of a unit, 16 bytes each; largest
+// is kept at the largest magnitude split so far.
 struct Planes {
     uintx4 q[3];
 };
-__device__ __forceinline__ void split_unit(const float (&v)[8], Planes &o) {
+__device__ __forceinline__ void split_unit(const float (&v)[8], Planes &o, float &largest) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+        largest = max3(largest, v[2 * j], v[2 * j + 1]);
         unsigned p[3];
         split_pair(v[2 * j], v[2 * j + 1], p);
 #pragma unroll
@@ -224,9 +259,10 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
                                                                         acc[i][b], 0, 0, 0);
     };
     Planes pl[U];
+    float largest = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        split_unit(raw[u], pl[u]);
+        split_unit(raw[u], pl[u], largest);
         load(u, 1);
     }
     for (int s = 0; s < stages; ++s) {
@@ -243,7 +279,7 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
         for (int t = 0; t < STEPS; ++t) {
             if (t + 1 < STEPS) read(t + 1, o[(t + 1) & 1]);
             if (t < U) {
-                split_unit(raw[t], pl[t]);
+                split_unit(raw[t], pl[t], largest);
                 load(t, s + 2);
             }
             mma(o[t & 1]);
@@ -259,31 +295,53 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
         }
     }
 
-    // Infinities, NaN and values that round up past bf16's largest leave NaN in
-    // the accumulators, and the bf16 MFMA flushes denormal planes, which counts
-    // only where whole tiles are tiny: such tiles run again on fp32 MFMAs.
-    float nan = 0.f, big = 0.f;
+    // Infinities, NaN and values that round up past bf16's largest leave NaN or
+    // infinities in the accumulators.  With any of them, or operands too small for their
+    // outputs, the workgroup's tile runs again on fp32 MFMAs: its operands are
+    // shared between the waves, so one vote decides for all.
+    float large = 0.f, small = kSmall;
 #pragma unroll
     for (int i = 0; i < TB; ++i)
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                nan = fmaf(acc[i][b][v], 0.f, nan);
-                big = fmaxf(big, fabsf(acc[i][b][v]));
+            for (int v = 0; v < 16; v += 2) {
+                large = max3(large, acc[i][b][v], acc[i][b][v + 1]);
+                small = min3(small, acc[i][b][v], acc[i][b][v + 1]);
             }
-    const bool bad = !(nan == 0.f) || (big > 0.f && big < 0x1p-80f);
+    const int vote = (__any(!(large < INFINITY)) ? 1 : 0) |
+                     (__any(!(largest < kLarge) || small < kSmall) ? 2 : 0);
+    unsigned *votes = reinterpret_cast<unsigned *>(lds);
     lds_barrier();
-    if (__any(bad)) {
-        if (lane == 0) reinterpret_cast<int *>(lds)[wp] = 1;
-    } else if (lane == 0) {
-        reinterpret_cast<int *>(lds)[wp] = 0;
-    }
+    if (lane == 0) votes[wp] = vote;
     lds_barrier();
     int again = 0;
-    for (int w = 0; w < a.wpx; ++w) again |= reinterpret_cast<const int *>(lds)[w];
+    for (int w = 0; w < a.wpx; ++w) again |= votes[w];
+    again = __builtin_amdgcn_readfirstlane(again);
+    if (again == 2) {
+        unsigned least[2] = {~0u, ~0u};           // of the image, of the weights
+        for (int s = 0; s < stages; ++s)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                load(u, s);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) least[u >= HU] = min(least[u >= HU], mag(raw[u][j]));
+            }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+            for (int d = 1; d < 64; d *= 2) least[k] = min(least[k], unsigned(__shfl_xor(int(least[k]), d)));
+            if (lane == 0) votes[4 + 4 * k + wp] = least[k];
+        }
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            for (int w = 0; w < a.wpx; ++w) least[k] = min(least[k], votes[4 + 4 * k + w]);
+        const bool lost = min(least[0], least[1]) < kExact || (least[0] >> 24) + (least[1] >> 24) < kWhole;
+        again = __builtin_amdgcn_readfirstlane(int(lost));
+    }
     lds_barrier();
-    if (__builtin_amdgcn_readfirstlane(again)) {
+    if (again & 1) {
         // the lane's coordinates anew, so that nothing of this path is kept in
         // registers through the loop above
         int ln = lane;

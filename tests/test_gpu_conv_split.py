@@ -144,3 +144,55 @@ def test_split_special_values(env, kind):
     # tile's largest output
     scale = np.abs(want[fin]).max()
     assert np.abs(got[fin] - want[fin]).max() <= 288 * 2.0 ** -24 * scale
+
+
+# a rectangle, ragged K, a band over three images in eight splits, stride 2
+GUARD_POINTS = [POINTS[0], POINTS[1], POINTS[4],
+                ((1, 16, 18, 18, 40, 3, 3, 2, 1), (32, 16, 8, 4, 2, 3))]
+
+
+def scaled(kind, x, w):
+    x, w = x.astype(np.float64), w.astype(np.float64)
+    if kind == "column":          # tiny pixels beside normal ones
+        x[:, :, :, 5] *= 1e-38
+        x[-1, :, 3, :] = 0        # and empty ones
+    elif kind == "channel":       # a tiny output channel beside normal ones
+        w[7] *= 1e-39
+        x *= 1e20
+    elif kind == "one":           # a single tiny operand that alone makes its outputs
+        x[:, :, 4:7, 4:7] = 0
+        x[0, 3, 5, 5] = 1.2345e-38
+        w *= 1e20
+    else:
+        sx, sw = map(float, kind.split("*"))
+        x *= sx
+        w *= sw
+    return x.astype(np.float32), w.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["1e-36*1e20", "1e-38*1e20", "1e-39*1e30", "1e-39*1", "1e20*1e-38",
+                                  "1e-16*1e-17", "1e-20*1e-22", "1e-30*1e30", "column", "channel",
+                                  "one"])
+@pytest.mark.parametrize("sh,knobs", GUARD_POINTS,
+                         ids=["x".join(map(str, p[0])) for p in GUARD_POINTS])
+def test_split_small_operands(env, sh, knobs, kind):
+    """Operands whose bf16 planes lose bits, or whose products leave the normal
+    range: every output within what n fp32 sums may lose (each rounds to 2^-24 of
+    at most sum |x w|, a few more for the product and the splits, and to 2^-149),
+    and the errors relative to sum |x w| no larger than the fp32 program's (2-norm;
+    1.1 as above)."""
+    torch, L = env
+    _, split, f32 = points(L, sh, knobs)
+    x, w = scaled(kind, *synthdata.conv_inputs(sh, "he"))
+    ref = ok.conv2d_f64(x, w, sh).ravel()
+    mag = ok.conv2d_f64(np.abs(x), np.abs(w), sh).ravel()
+    n = sh[1] * 9 + 8
+    xd, wd = dev(torch, x), dev(torch, w)
+    print("conv split small", sh, knobs, kind, flush=True)
+    e = [np.abs(run(torch, L, s, xd, wd, ref.size) - ref) for s in (split, f32)]
+    some = mag > 0
+    rel = [np.linalg.norm(v[some] / mag[some]) / np.sqrt(some.sum()) * 2.0 ** 24 for v in e]
+    print(f"  error in 2^-24 sum|xw|: {rel[0]:.3g}, fp32 MFMA {rel[1]:.3g}")
+    assert (e[0] <= n * (2.0 ** -24 * mag + 2.0 ** -149)).all()
+    assert (e[0][~some] == 0).all()
+    assert rel[0] <= 1.1 * rel[1]
