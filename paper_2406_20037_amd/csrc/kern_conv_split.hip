@@ -32,6 +32,8 @@
 // way 361.  VGG-16 at batch 16, against the fp32 program of the same schedule:
 // 64x224x224 532 -> 336 us, 512x28x28 (8 reduction splits, their reduce
 // included) 571 -> 351, 512x14x14 (16 splits) 177 -> 131.
+#include <type_traits>
+
 #include "kern_conv_tile.h"
 
 namespace ds {
@@ -258,27 +260,32 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
                     acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.A[i][pa[e]], o.B[b][pb[e]],
                                                                         acc[i][b], 0, 0, 0);
     };
+    // The last stage has no next one to split: a build of its own saves that work.
+    // One stage of eight channels, 8x8x100x100: 16.6 -> 14.7 us, where the fp32
+    // program takes 14.5; 14x14x512 in 16 splits of four stages: 1%.  For waves of
+    // 64 x 64 it spills, and their stages slow down by 1 to 4%.
+    constexpr bool TAIL = TB * NB < 4;
     Planes pl[U];
     float largest = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         split_unit(raw[u], pl[u], largest);
-        load(u, 1);
+        if (!TAIL || stages > 1) load(u, 1);
     }
-    for (int s = 0; s < stages; ++s) {
+    // each step's MFMAs, with the split of one unit of the next stage and the
+    // loads of the one after it between them
+    auto run_stage = [&]<bool LAST>(std::bool_constant<LAST>, int s) {
         if (s > 0) lds_barrier();       // every wave is past its reads of the last stage
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (u >= HU || src[u] >= 0) store_unit(dst(u), pl[u]);
         lds_barrier();
-        // each step's MFMAs, with the split of one unit of the next stage and
-        // the loads of the one after it between them
         Ops o[2];
         read(0, o[0]);
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
             if (t + 1 < STEPS) read(t + 1, o[(t + 1) & 1]);
-            if (t < U) {
+            if (!LAST && t < U) {
                 split_unit(raw[t], pl[t], largest);
                 load(t, s + 2);
             }
@@ -288,12 +295,15 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
             for (int m = 0; m < NM; ++m) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (m < 3 * (TB + NB)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if (LAST) continue;
                 __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
                 if (m >= NM - 8) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
+    };
+    for (int s = 0; s < stages - TAIL; ++s) run_stage(std::false_type{}, s);
+    if (TAIL) run_stage(std::true_type{}, stages - 1);
 
     // Infinities, NaN and values that round up past bf16's largest leave NaN or
     // infinities in the accumulators.  With any of them, or operands too small for their
