@@ -10,7 +10,8 @@
 // that was not written (unless only discarded outputs depend on it); every
 // output is written exactly once (per split); each output tile counts one
 // arrival per non-empty split; and the fp64 result of the replayed
-// multiply-adds equals a direct convolution.  The replay mirrors the
+// multiply-adds equals a direct convolution.  Points with a build for their
+// filter size walk its rows of taps.  The replay mirrors the
 // kernel's arithmetic by hand: a change to one needs the same change here.
 //
 // stdin, one schedule per line:
@@ -249,16 +250,65 @@ bool replay(const int64_t *sh, int tk, int th, int tw, int tc, int depth, int ks
         std::vector<double> acc(size_t(nwave) * TKB * NPB * 256, 0.0);
         const int sa = 4 * KG * RS, sb = 4 * KG * a.cs;
         const int tg = (a.t4 / (KG * U)) * RS;
+        // LDS offsets of a wave group's steps, in the order it multiplies them, and of
+        // the read past the last one
+        struct Step {
+            int oa, ob;
+        };
+        auto quad_steps = [&](int g) {
+            std::vector<Step> out;
+            for (int t = 0; t < tg; ++t) {
+                const int cq = fdv(t, a.f_rs), rs = t - cq * RS;
+                const int r = fdv(rs, a.f_s), s = rs - r * S;
+                const int q = 4 * (cq * U * KG + g);
+                out.push_back({q * RS + rs, q * a.cs + r * a.ws + s});
+            }
+            out.push_back(out.back());
+            return out;
+        };
+        // the FS x FS builds: rows of taps from one address, two operand sets in
+        // turn, each read one step before it is multiplied
+        auto row_steps = [&](int g) {
+            std::vector<Step> out;
+            const int SA = 4 * KG * S * S, nrow = (a.t4 / (KG * U)) * S;
+            int pa = 4 * g * S * S, pb = 4 * g * a.cs;
+            Step o[2];
+            auto tap = [&](int s, Step &nx) { nx = {pa + s, pb + s}; };
+            int r = 0, left = nrow;
+            auto row = [&](int P) {
+                for (int s = 0; s < S; ++s) {
+                    Step &nx = o[(P * S + s + 1) & 1];
+                    if (s + 1 < S) {
+                        tap(s + 1, nx);
+                    } else {
+                        const bool end = --left == 0, wrap = ++r == S;
+                        r = wrap ? 0 : r;
+                        pa += end ? 0 : wrap ? U * SA - (S - 1) * S : S;
+                        pb += end ? 0 : wrap ? U * sb - (S - 1) * a.ws : a.ws;
+                        tap(0, nx);
+                    }
+                    out.push_back(o[(P * S + s) & 1]);
+                }
+            };
+            tap(0, o[0]);
+            while (left >= 2) {
+                row(0);
+                row(1);
+            }
+            if (left > 0) row(0);
+            out.push_back(o[(nrow * S) & 1]);
+            return out;
+        };
+        const bool rows_build = R == S && conv2_rows(TKB, NPB, U, KG, a.rc, S);
         issue(ci0, 0);
         for (int ci = ci0; ci < ci1; ++ci) {
             const int bo = ((ci - ci0) & 1) * a.buf;
             for (int wu = 0; wu < nwave; ++wu) {
                 const int g = wu >> a.lwpx;
-                for (int t = 0; t < tg; ++t) {
-                    const int cq = fdv(t, a.f_rs), rs = t - cq * RS;
-                    const int r = fdv(rs, a.f_s), s = rs - r * S;
-                    const int q = 4 * (cq * U * KG + g);
-                    const int oa = q * RS + rs, ob = q * a.cs + r * a.ws + s;
+                const std::vector<Step> steps = rows_build ? row_steps(g) : quad_steps(g);
+                CHECK(int(steps.size()) == tg + 1, "%zu steps of %d", steps.size(), tg + 1);
+                for (int t = 0; t < int(steps.size()); ++t) {
+                    const int oa = steps[t].oa, ob = steps[t].ob;
                     for (int u = 0; u < U; ++u)
                         for (int i = 0; i < TKB; ++i)
                             for (int bk = 0; bk < NPB; ++bk)
@@ -271,6 +321,7 @@ bool replay(const int64_t *sh, int tk, int th, int tw, int tc, int depth, int ks
                                             const int ib = bo + bbase[id] + ob + u * sb;
                                             CHECK(ia >= bo && ia < bo + a.bufw, "weight read at %d outside [%d, %d)", ia, bo, bo + a.bufw);
                                             CHECK(ib >= bo + a.bufw && ib < bo + a.buf, "halo read at %d outside [%d, %d)", ib, bo + a.bufw, bo + a.buf);
+                                            if (t == tg) continue;
                                             const double av = ia >= 0 && ia < lds_f ? lds[ia] : NAN;
                                             const double bv = ib >= 0 && ib < lds_f ? lds[ib] : NAN;
                                             if (kt * a.tk + i * 16 + m < K && pvalid[id])
@@ -377,8 +428,8 @@ bool replay(const int64_t *sh, int tk, int th, int tw, int tc, int depth, int ks
         maxref = std::max(maxref, std::fabs(ref));
     }
     CHECK(maxerr <= 1e-9 * std::max(1.0, maxref), "max error %g (max |ref| %g)", maxerr, maxref);
-    snprintf(summary, nsum, "band=%d tkb=%d npb=%d u=%d kg=%d ksw=%d grid=%ld lds=%d err=%.2g", a.band, TKB,
-             NPB, U, KG, a.ksw, (long)grid, int(c.lds), maxerr);
+    snprintf(summary, nsum, "band=%d rows=%d tkb=%d npb=%d u=%d kg=%d ksw=%d grid=%ld lds=%d err=%.2g", a.band,
+             R == S && conv2_rows(TKB, NPB, U, KG, a.rc, S) ? S : 0, TKB, NPB, U, KG, a.ksw, (long)grid, int(c.lds), maxerr);
     return g_errors == 0;
 }
 

@@ -14,6 +14,7 @@ oracle's hand-worked pins do not cover.
 
 Shapes: bands crossing image boundaries, several images per band, strides 2,
 3 input channels, no padding, 5x5 filters, W not a multiple of 4, ragged K.
+Points whose filter size has a build of its own (3x3, 5x5) walk its rows of taps.
 Points: sampled valid mfma 2 and 3 points of each shape; a third of them also
 replayed with both operands 4 bytes off a 16-byte boundary.  Split shapes:
 batch-1 layers with many channels and few output pixels, replayed at 16 and
@@ -44,6 +45,8 @@ SHAPES = [
     (2, 32, 16, 16, 32, 3, 3, 1, 1),
     (1, 8, 5, 40, 16, 3, 3, 1, 1),
     (2, 4, 30, 30, 17, 5, 5, 1, 2),
+    (1, 37, 13, 14, 40, 5, 5, 1, 2),
+    (1, 64, 9, 9, 32, 3, 3, 2, 1),
 ]
 PER_SHAPE = 14
 SPLIT_SHAPES = [
@@ -78,6 +81,7 @@ def _replay(replay_bin, s, sh, pick):
     out = r.stdout.strip().splitlines()
     assert r.returncode == 0 and len(out) == len(lines) and all(o.startswith("ok") for o in out), (
         f"{lines[len(out) - 1] if out else lines[0]}: {out[-1:] } {r.stderr[-2000:]}")
+    return out
 
 
 @pytest.mark.parametrize("sh", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
@@ -89,7 +93,10 @@ def test_conv2_index_replay(replay_bin, sh):
     band = [p for p in pts if s.knobs(p)["mfma"] == 3]
     rect = [p for p in pts if s.knobs(p)["mfma"] == 2]
     pick = rng.sample(band, min(PER_SHAPE, len(band))) + rng.sample(rect, min(PER_SHAPE // 2, len(rect)))
-    _replay(replay_bin, s, sh, pick)
+    out = _replay(replay_bin, s, sh, pick)
+    # 3x3 and 5x5 filters have builds that walk rows of taps, the others none
+    rows = {int(o.split("rows=")[1].split()[0]) for o in out}
+    assert (sh[5] in rows) if sh[5] in (3, 5) else rows == {0}, rows
 
 
 @pytest.mark.parametrize("sh", SPLIT_SHAPES, ids=["x".join(map(str, s)) for s in SPLIT_SHAPES])

@@ -2,7 +2,8 @@
 
 1. Reachable instances.  For every task of the five workloads (conv 3x3 C64
    56x56, matmul 1024^3, conv 7x7/2 C3 224x224, the ResNet-50 layers and FC,
-   the VGG-16 layers) the library lists the template instance each valid
+   the VGG-16 layers) and a 5x5 layer, whose filter size has builds of its own
+   that no workload reaches, the library lists the template instance each valid
    lattice point selects (Definition 1: an annotated sketch is a concrete
    program).  Each distinct instance is launched once, at the first point (in
    key order) of the smallest workload that reaches it, on small-integer
@@ -57,10 +58,14 @@ def out_elems(op, sh):
     return sh[0] * sh[1]
 
 
+# every 5x5 build with chunks that fit LDS
+CONV5X5 = ("conv5x5_c128_56", wl.OP_CONV, (1, 128, 56, 56, 64, 5, 5, 1, 2))
+
+
 def first_reach(L):
     """{instance: (task name, op, shape, key)} over the tasks, smallest
     problem first, and the set of instances per family."""
-    tasks = sorted(all_tasks(), key=lambda t: (wl.flops(t[1], t[2]), t[0]))
+    tasks = sorted(all_tasks() + [CONV5X5], key=lambda t: (wl.flops(t[1], t[2]), t[0]))
     first = {}
     for name, op, sh in tasks:
         keys, inst, _ = L.Space(op, sh).programs()
@@ -78,6 +83,7 @@ def test_every_reachable_instance_bit_exact_and_within_its_budget(env):
     for inst, (name, op, sh, key) in first.items():
         by_task[(name, op, sh)].append((inst, key))
     tested = collections.Counter()
+    sizes = collections.Counter()
     reach = collections.Counter(FAMILY[i // 4096] for i in first)
     for (name, op, sh), items in sorted(by_task.items(), key=lambda t: wl.flops(t[0][1], t[0][2])):
         if op == wl.OP_CONV:
@@ -112,10 +118,15 @@ def test_every_reachable_instance_bit_exact_and_within_its_budget(env):
             got = yb[:n][idx_d].cpu().numpy().astype(np.float64)
             assert np.array_equal(got, ref), f"{what}: differs from the oracle"
             tested[FAMILY[info["family"]]] += 1
+            if info["family"] == 5:
+                sizes[tuple(info["params"][5:])] += 1
         del xd, wd, yb
     for fam in sorted(reach):
         print(f"{fam}: reachable {reach[fam]}, tested {tested[fam]}", flush=True)
+    print(f"conv_mfma2 sixth parameter: {dict(sizes)}", flush=True)
     assert tested == reach
+    # both filter sizes' builds, the split-operand and the few-channel kernels
+    assert sizes[(3,)] > 100 and sizes[(5,)] > 60 and sizes[(1,)] == 4 and sizes[(2,)] == 6
     assert sum(reach.values()) == len(first) > 1000
 
 
