@@ -28,6 +28,8 @@ SHAPES = [
     (1, 8, 5, 40, 32, 3, 3, 1, 1),
     (5, 64, 9, 9, 64, 3, 3, 1, 1),
     (1, 32, 40, 33, 64, 3, 3, 1, 2),
+    (1, 16, 18, 18, 32, 3, 3, 2, 1),
+    (2, 24, 10, 20, 40, 3, 3, 2, 1),
 ]
 PER_SHAPE = 10
 

@@ -12,7 +12,8 @@ filters, whole groups of eight channels) on the GPU.
   for its spread.
 * Values the bf16 planes cannot hold (infinities, NaN, floats that round past
   the largest bf16, tiles of tiny values): the same outputs as the fp32
-  program, non-finite where and as it has them.
+  program, non-finite where and as it has them; rectangles, bands over several
+  images with a reduction split and ragged channels, stride 2.
 """
 import numpy as np
 import pytest
@@ -35,6 +36,8 @@ POINTS = [
     ((5, 16, 9, 9, 64, 3, 3, 1, 1), (64, 16, 16, 4, 2, 3)),
     ((2, 40, 13, 11, 48, 3, 3, 1, 1), (32, 16, 8, 4, 1, 3)),
     ((1, 48, 12, 40, 32, 3, 3, 1, 1), (32, 4, 64, 4, 2, 3)),
+    ((1, 16, 18, 18, 32, 3, 3, 2, 1), (32, 16, 8, 4, 1, 3)),
+    ((2, 32, 10, 20, 40, 3, 3, 2, 1), (32, 8, 16, 4, 2, 3)),
 ]
 
 
@@ -113,13 +116,19 @@ def test_split_no_less_precise_than_fp32_mfma(env, sh, knobs, scale):
     assert e[0] <= 1.1 * e[1]
 
 
+# a rectangle, a band over three images in eight splits with ragged channels, and
+# one of stride 2
+SPECIAL_POINTS = [POINTS[0], POINTS[4], POINTS[9]]
+
+
 @pytest.mark.parametrize("kind", ["inf", "nan", "max", "tiny", "winf"])
-def test_split_special_values(env, kind):
+@pytest.mark.parametrize("sh,knobs", SPECIAL_POINTS,
+                         ids=["x".join(map(str, p[0])) for p in SPECIAL_POINTS])
+def test_split_special_values(env, sh, knobs, kind):
     torch, L = env
-    sh, knobs = POINTS[0]
     _, split, f32 = points(L, sh, knobs)
     x, w = synthdata.conv_inputs(sh, "he")
-    at = (1, 5, 13, 9)
+    at = (1, 5, min(13, sh[2] - 1), 9)
     if kind == "inf":
         x[at] = np.inf
         x[0, 0, 0, 0] = -np.inf
@@ -132,18 +141,19 @@ def test_split_special_values(env, kind):
         x *= np.float32(1e-36)
     else:
         w[3, 2, 1, 1] = np.inf
-    n = sh[0] * sh[4] * sh[2] * sh[3]
+    P, Q = synthdata.conv_out_hw(sh[2], sh[3], sh[5], sh[6], sh[7], sh[8])
+    n = sh[0] * sh[4] * P * Q
     xd, wd = dev(torch, x), dev(torch, w)
-    print("conv split special", kind, flush=True)
+    print("conv split special", sh, knobs, kind, flush=True)
     got, want = (run(torch, L, s, xd, wd, n) for s in (split, f32))
     assert np.array_equal(np.isnan(got), np.isnan(want))
     inf = np.isinf(want)
     assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
     fin = np.isfinite(want)
-    # both within fp32 rounding of the same sums: 288 terms, each below the
-    # tile's largest output
+    # both within fp32 rounding of the same sums: 9 terms a channel, each below
+    # the tile's largest output
     scale = np.abs(want[fin]).max()
-    assert np.abs(got[fin] - want[fin]).max() <= 288 * 2.0 ** -24 * scale
+    assert np.abs(got[fin] - want[fin]).max() <= 9 * sh[1] * 2.0 ** -24 * scale
 
 
 # a rectangle, ragged K, a band over three images in eight splits, stride 2
