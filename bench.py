@@ -16,7 +16,8 @@ layers give each layer's average launch duration inside the same timed
 passes; the dominant layer carries the `roofline` object.  The other four
 workloads are timed the same way after the headline (a pass = every tuned
 kernel of the workload, each as often as the network runs it) and reported
-in `configs`, with their tuning counts and wall-clock.
+in `configs`, with their tuning counts and wall-clock.  The JSON line keeps to
+what fits the 16 KB a log's tail holds; every task's full row goes to stderr.
 
 The CPU baseline leg runs the fp64 oracle once over every task of the five
 workloads on the host cores, and checks every tuned kernel's output against
@@ -102,6 +103,17 @@ def kernel_name(space, idx):
         params = (params + [0])[:6]      # filter size of the build, 0: any
     args = ", ".join(str(v) for v in params)
     return f"{FAMILY_NAME[info['family']]}<{args}>"
+
+
+def brief(row):
+    """A task's row as the JSON line has it."""
+    keep = ("name", "count", "shape", "kernel", "tuned_us", "launch_us", "cold_us",
+            "frac_of_roofline")
+    out = {k: row[k] for k in keep if k in row}
+    out["schedule"] = ",".join(f"{k}={v}" for k, v in row["best_schedule"].items())
+    if row.get("max_rel_err") is not None:
+        out["max_rel_err"] = float(f"{row['max_rel_err']:.2g}")
+    return out
 
 
 def peak_tflops(kernel):
@@ -345,12 +357,18 @@ def main(argv=None):
                 rows[-1]["launch_us"] = round(launch_ms[i] * 1e3, 3)
             if args.flush:
                 rows[-1]["cold_us"] = round(cold_time(L, task, stream) * 1e3, 3)
+            log("task", json.dumps(rows[-1]))
         dom = max(range(len(rows)), key=lambda i: rows[i]["count"] * rows[i]["tuned_us"])
         pm = pass_ms[n]
         configs.append(dict(
             config=wk.config, workload=DESCRIPTION[n], name=n,
             gflops=round(wk.flops / (pm * 1e-3) / 1e9, 1),
             frac_of_fp32_peak=round(wk.flops / (pm * 1e-3) / (PEAK_FP32_TFLOPS * 1e12), 4),
+            # each task's products at the rate its kernel's matrix instructions have
+            # (split-operand kernels can pass 1.0 of the fp32 one)
+            frac_of_kernel_peaks=round(sum(
+                t["count"] * t["flops"] / (peak_tflops(t["kernel"]) * 1e12) for t in wk.T)
+                / (pm * 1e-3), 4),
             pass_us=round(pm * 1e3, 3),
             pass_timing=("host launches, events" if n == head else
                          "graph replays (passes back to back in one graph), events"),
@@ -359,7 +377,7 @@ def main(argv=None):
             n_explore_measured=sum(r["n_explore_measured"] for r in rows),
             n_droplet_measured=sum(r["n_droplet_measured"] for r in rows),
             tuning_wall_s=round(wk.tune_wall, 2),
-            tasks=rows))
+            tasks=[brief(r) for r in rows]))
 
     # Roofline of the headline's dominant kernel, from the timed passes.
     hc = next(c for c in configs if c["name"] == head)
@@ -431,7 +449,7 @@ def main(argv=None):
             "tolerance": TOL, "max_rel_err": worst,
             "status": "ok" if worst <= TOL else "FAIL"},
     }
-    print(json.dumps(out), flush=True)
+    print(json.dumps(out, separators=(",", ":")), flush=True)
     if worst is not None and not worst <= TOL:
         log(f"a tuned kernel fails the oracle check: max relative error {worst:.3g} > {TOL}")
         return 3

@@ -37,6 +37,17 @@ def test_json_line_contract():
     assert d["n_gpus"] == 1 and d["steps"] == 2 and d["warmup"] == 1
     assert d["value"] > 0 and d["ms_per_step"] > 0 and d["higher_is_better"] is True
     assert d["unit"] == "GFLOP/s" and d["dtype"] == "f32" and d["vs_baseline"] is None
+    # the default run's 40 task rows leave the line below the 16000 characters a
+    # record of its output keeps; the full rows are on stderr
+    rows = [t for c in d["configs"] for t in c["tasks"]]
+    # (four more workloads of 600 characters beside their rows, the fields of 40 rows
+    # at their longest, 280)
+    size = [len(json.dumps(t, separators=(",", ":"))) for t in rows]
+    assert max(size) < 280
+    assert len(lines[0]) - sum(size) + 4 * 600 + 40 * 280 < 16000
+    full = [json.loads(l[5:]) for l in r.stderr.splitlines() if l.startswith("task {")]
+    assert [t["name"] for t in full] == [t["name"] for t in rows]
+    assert all("best_schedule" in t and "n_explore_measured" in t for t in full)
     # value is the pass's algorithmic flop over its mean time
     from synthdata import workloads as wl
     tasks = [c for c in d["configs"] if c["name"] == "vgg16"][0]["tasks"]
