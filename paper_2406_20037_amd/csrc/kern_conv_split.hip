@@ -311,9 +311,16 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
     // shared between the waves, so one vote decides for all.
     float large = 0.f, small = kSmall;
 #pragma unroll
-    for (int i = 0; i < TB; ++i)
+    for (int b = 0; b < NB; ++b) {
+        // A rectangle's pixels past the image are zeros that nobody reads, and no
+        // reason to look again (8x16x100x90 in rectangles of 8x16: 45.2 us with them,
+        // 38.4 without).
+        const int pix = (wp * NB + b) * 32 + li;
+        const bool kept = a.band || (T.pt * a.th + (pix >> a.ltw) < a.P &&
+                                     T.qt * a.tw + (pix & (a.tw - 1)) < a.Q);
+        float least = kSmall;
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int i = 0; i < TB; ++i)
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 large = max3(large, acc[i][b][v], acc[i][b][v + 1]);
