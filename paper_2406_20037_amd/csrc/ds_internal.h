@@ -366,7 +366,12 @@ inline Conv2Shape conv2_setup(const int64_t *sh, int tk, int th, int tw, int tc,
 //     three channels padded to eight the fp32 loop is faster (3x64x224x224 at
 //     batch 16: 69 us against 72) and more precise;
 //   - at most two halo positions per thread: they are held in registers twice
-//     (next stage's planes, the one after in fp32) and all 256 are in use.
+//     (next stage's planes, the one after in fp32) and all 256 are in use;
+//   - not rectangles of 32 pixels a wave in splits of a single stage, where the fp32
+//     program copies the weights 16 bytes at a time: what a weight is multiplied with
+//     is too little there for what splitting it costs (of 204 sampled points 37 were
+//     3 to 13% slower than on the fp32 program; of 3906 points beside them none, and
+//     1.4 times as fast in the geometric mean).
 constexpr int kConvSplitHalo = 2;         // halo units per thread of a stage
 constexpr int kConvSplitRow = 496;        // LDS bytes of a weight row: 10 taps of 48, and 16
 constexpr int kConvSplitSlots = 4;
@@ -375,6 +380,7 @@ inline bool conv2_split_setup(Conv2Args &a, const Conv2Shape &c, int64_t *lds) {
     if (a.R != 3 || a.S != 3 || c.u != 1 || c.kg != 1 || c.tkb < 2 || c.npb < 2 || c.npb > 4 ||
         a.wpx != 4 || a.C % 8 != 0 || (int64_t(a.cps) * a.tc) % 8 != 0)
         return false;
+    if (!a.band && a.vw && c.npb == 2 && a.ksw > 1 && int64_t(a.cps) * a.tc == 8) return false;
     a.sws = ((a.band ? a.Q : a.tw) - 1) * a.st + a.S;
     const int64_t nh = int64_t(a.hs) * a.sws;
     if (nh > kConvSplitHalo * c.threads) return false;

@@ -6,6 +6,10 @@ tensors, LDS units inside the workgroup's LDS and written before they are read,
 every output written once per split, and the fp64 result of the replayed
 multiply-adds equal to a direct convolution.  Shapes: strides, padding, ragged
 K, odd image sizes, reduction splits, bands across images.
+
+Also which points take the kernel at all: rectangles of 32 pixels a wave in splits
+of a single stage, whose weights the fp32 program copies 16 bytes at a time, stay on
+that program.
 """
 import os
 import random
@@ -68,3 +72,26 @@ def test_conv_split_index_replay(replay_bin, sh):
     assert r.returncode == 0 and len(out) == len(lines), (
         f"{lines[len(out) - 1] if out else lines[0]}: {out[-1:]} {r.stderr[-2000:]}")
     assert any(o.startswith("ok") for o in out), out
+
+
+# tile knobs (tk, th, tw, tc, ks, mfma, vec); takes the split-operand kernel?
+ROUTES = [
+    ((16, 64, 112, 112, 128, 3, 3, 1, 1), (64, 32, 4, 4, 8, 2, 4), False),
+    ((16, 64, 112, 112, 128, 3, 3, 1, 1), (32, 32, 4, 4, 8, 2, 4), False),
+    ((16, 64, 112, 112, 128, 3, 3, 1, 1), (64, 32, 4, 4, 4, 2, 4), True),    # two stages
+    ((16, 64, 112, 112, 128, 3, 3, 1, 1), (64, 32, 8, 4, 8, 2, 4), True),    # 64 pixels a wave
+    ((3, 40, 61, 53, 90, 3, 3, 1, 1), (64, 8, 16, 4, 8, 2, 4), False),
+    ((3, 40, 61, 53, 90, 3, 3, 1, 1), (64, 8, 16, 4, 8, 2, 1), True),        # 4-byte copies
+    ((16, 8, 56, 56, 128, 3, 3, 1, 1), (64, 32, 4, 8, 1, 2, 4), True),       # no split
+    ((16, 256, 14, 14, 512, 3, 3, 1, 1), (64, 16, 8, 4, 32, 3, 4), True),    # a band
+]
+
+
+@pytest.mark.parametrize("sh,knobs,taken", ROUTES)
+def test_single_stage_rectangles_keep_the_fp32_program(sh, knobs, taken):
+    from paper_2406_20037_amd import _lib as L
+    space = L.Space(L.DS_OP_CONV2D_NCHW, sh)
+    kn = dict(zip(("tk", "th", "tw", "tc", "ks", "mfma", "vec"), knobs), unroll=0, lds=1)
+    s = space.sched_of(**kn)
+    assert space.valid(s.index())
+    assert (space.kernel_info(s.index())["params"][5:] == [1]) == taken
