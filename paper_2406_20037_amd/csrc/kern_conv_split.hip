@@ -324,8 +324,10 @@ __global__ __launch_bounds__(256, 2) void conv_split(Conv2Args a) {
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 large = max3(large, acc[i][b][v], acc[i][b][v + 1]);
-                small = min3(small, acc[i][b][v], acc[i][b][v + 1]);
+                least = min3(least, acc[i][b][v], acc[i][b][v + 1]);
             }
+        small = kept ? __builtin_elementwise_minimum(small, least) : small;
+    }
     const int vote = (__any(!(large < INFINITY)) ? 1 : 0) |
                      (__any(!(largest < kLarge) || small < kSmall) ? 2 : 0);
     unsigned *votes = reinterpret_cast<unsigned *>(lds);
