@@ -752,12 +752,13 @@ __global__ __launch_bounds__(256 * KG) void mm_mfma(MatmulArgs a) {
 // A few rows of C (M <= 4, the matrix-vector products of a classifier at small
 // batch): a workgroup owns 16 columns and the whole reduction, so a split (ks >=
 // 2) needs no partials and no second launch.  Its 128 * ks threads take four
-// columns each (16 bytes of a row of B) of every (32 * ks)-th row, eight rows in
+// columns each (16 bytes of a row of B) of every (32 * ks)-th row, up to four rows in
 // flight per thread (one with unroll 0), and meet by lane exchange and LDS.
-// Bound by the latency of that one round of loads: 63 workgroups hold all of
-// 2048x1000 in flight at once.  1x1000x2048, ks 8: 8.3 us in two launches (504
-// 16x16 tiles, reduce) before, 5.75 now; 120 points of six shapes
-// with 1 to 4 rows 1.95 times as fast (geometric mean, none slower).
+// Bound by the latency of the loads (63 workgroups hold 256 rows of 2048x1000 in
+// flight at once), large matrices by their bytes.  In a graph, against the tiles
+// and reduce launch of the same point: 1x1000x2048, ks 8, 7.8 -> 3.6 us; 4x1000x2048
+// 8.1 -> 4.5; 1x4096x4096 32.0 -> 13.7 (4.9 TB/s).  2640 points of 140 shapes with 1
+// to 4 rows 2.4 times as fast (geometric mean; the least 1.4).
 template <int MR>
 __global__ __launch_bounds__(1024) void mm_rows(MatmulArgs a) {
     __shared__ float red[16][MR][16];
@@ -769,38 +770,59 @@ __global__ __launch_bounds__(1024) void mm_rows(MatmulArgs a) {
     floatx4 acc[MR];
 #pragma unroll
     for (int m = 0; m < MR; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto rows = [&]<int D>(std::integral_constant<int, D>) {
-        for (int k0 = r0; k0 < a.K; k0 += D * step) {
-            floatx4 b[D];
-            float av[D][MR];
+    // D rows, one step apart, from row k on, all loaded before the first is used
+    auto rows = [&]<int D>(std::integral_constant<int, D>, int k) {
+        floatx4 b[D];
+        float av[D][MR];
 #pragma unroll
-            for (int u = 0; u < D; ++u) {
-                const int k = min(k0 + u * step, a.K - 1);
-                b[u] = *reinterpret_cast<const floatx4 *>(B + (size_t)k * a.N);
+        for (int u = 0; u < D; ++u) {
+            b[u] = *reinterpret_cast<const floatx4 *>(B + (size_t)(k + u * step) * a.N);
 #pragma unroll
-                for (int m = 0; m < MR; ++m) av[u][m] = a.A[(size_t)min(m, a.M - 1) * a.K + k];
-            }
-#pragma unroll
-            for (int u = 0; u < D; ++u) {
-                if (k0 + u * step >= a.K) break;
-#pragma unroll
-                for (int m = 0; m < MR; ++m)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[m][j] = fmaf(av[u][m], b[u][j], acc[m][j]);
-            }
+            for (int m = 0; m < MR; ++m) av[u][m] = a.A[(size_t)min(m, a.M - 1) * a.K + k + u * step];
         }
+        // (left alone, the scheduler loads a row at a time to save registers)
+        if constexpr (D > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < D; ++u)
+#pragma unroll
+            for (int m = 0; m < MR; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[m][j] = fmaf(av[u][m], b[u][j], acc[m][j]);
     };
-    if (a.uf >= 8) rows(std::integral_constant<int, 8>{});
-    else rows(std::integral_constant<int, 1>{});
-    // lanes 4 apart hold the same columns
+    // every thread has `left` rows, the first K % step of them one more
+    int k = r0, left = a.K / step;
+    auto blocks = [&]<int D>(std::integral_constant<int, D> d) {
+        if (a.uf < D) return;
+        for (; left >= D; left -= D, k += D * step) rows(d, k);
+    };
+    blocks(std::integral_constant<int, 4>{});
+    blocks(std::integral_constant<int, 2>{});
+    blocks(std::integral_constant<int, 1>{});
+    if (k < a.K) rows(std::integral_constant<int, 1>{}, k);
+    // Lanes 4 apart hold the same columns.  Each exchange halves the sums a lane
+    // holds (it sends the half its partner keeps) until one is left, so a wave's 16
+    // rows meet in 5 to 15 exchanges instead of the 16 to 64 of whole sums.
+    float v[4 * MR];
 #pragma unroll
-    for (int m = 0; m < MR; ++m)
+    for (int e = 0; e < 4 * MR; ++e) v[e] = acc[e / 4][e % 4];
+    int at = 0;                                   // sum the lane is left with
+    bool own = true;                              // (one of its copies)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+    for (int d = 4, n = 4 * MR; d < 64; d *= 2, n = n > 1 ? n / 2 : 1) {
+        const bool up = lane & d;
+        if (n > 1) {
 #pragma unroll
-            for (int d = 4; d < 64; d *= 2) acc[m][j] += __shfl_xor(acc[m][j], d);
-            if (lane < 4) red[wid][m][4 * lane + j] = acc[m][j];
+            for (int e = 0; e < n / 2; ++e) {
+                const float lo = v[e], hi = v[e + n / 2];
+                v[e] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, d);
+            }
+            at += up ? n / 2 : 0;
+        } else {
+            v[0] += __shfl_xor(v[0], d);
+            own = own && !up;
         }
+    }
+    if (own) red[wid][at >> 2][4 * (lane & 3) + (at & 3)] = v[0];
     __syncthreads();
     if (tid < 16 * MR) {
         const int m = tid >> 4, c = tid & 15;
