@@ -629,14 +629,17 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         a.vecA = vec == 4 && (a.K % 4 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0);
         a.vecB = vec == 4 && (a.N % 4 == 0) && (reinterpret_cast<uintptr_t>(w) % 16 == 0);
         a.direct = a.vecA && a.vecB && a.M % bm == 0 && a.N % bn == 0 && a.K % bk == 0;
-        // 4-byte copies lose to loads through registers where those take one
-        // operand 16 bytes at a time and the checked copies of a ragged last
-        // K-tile are most of a short loop (64x2000x129: 9.3 us against 7.4 at 3
-        // K-tiles, 6.9 against 6.7 at 5, even at 9)
+        // 4-byte copies lose to loads through registers where the checked copies of a
+        // ragged last K-tile are most of a short loop: where the loads take one
+        // operand 16 bytes at a time (64x2000x129: 9.3 us against 7.4 at 3 K-tiles, 6.9
+        // against 6.7 at 5, even at 9), and of 4-byte loads where that tile is the
+        // only one (95 sampled points: 1.3% slower in the mean, the worst 18%; with
+        // two tiles 3% faster)
         const bool reach = int64_t(std::min(a.M, bm)) * a.K < (int64_t(1) << 30) &&
                            int64_t(bk) * a.N < (int64_t(1) << 30);
-        const bool mixed = a.vecA != a.vecB && a.K % bk != 0 && a.kps < 8;
-        a.pipe = reach && !mixed ? (a.vecA && a.vecB ? 4 : 1) : 0;
+        const bool brief = a.K % bk != 0 && a.kps < (a.vecA != a.vecB ? 8 : 2);
+        a.pipe = a.vecA && a.vecB ? 4 : brief ? 0 : 1;
+        if (!reach) a.pipe = 0;
         a.gm = mm_group_rows(a.tiles_m, a.tiles_n, a.ks, bm, bn);
         plan.func = mfma ? mm_mfma_instance(g.t0, g.t1, bk, g.unroll_eff, dbuf, kg)
                          : mm_valu_instance(g.t0, g.t1, bk, g.unroll_eff, dbuf);

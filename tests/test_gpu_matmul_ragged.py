@@ -11,8 +11,10 @@ from oracle import space as osp
 
 pytestmark = pytest.mark.gpu
 
-# odd everything; 16-byte rows with ragged tiles; K below and just past a K-tile
-SHAPES = [(257, 195, 203), (260, 196, 204), (130, 129, 15), (65, 71, 65), (129, 260, 68)]
+# odd everything; 16-byte rows with ragged tiles; K below and just past a K-tile; rows
+# of B or of A alone in 16-byte groups, few K-tiles (staged through registers) and many
+SHAPES = [(257, 195, 203), (260, 196, 204), (130, 129, 15), (65, 71, 65), (129, 260, 68),
+          (65, 72, 66), (66, 71, 264), (70, 132, 151)]
 
 
 def run(torch, L, s, a, b, n):
