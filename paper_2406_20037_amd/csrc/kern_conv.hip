@@ -858,9 +858,8 @@ constexpr int conv2_waves(int tkb, int npb, int u, int kg, int rc) {
 // to eight blocks a wave (four for 5x5): a step of a small tile spends more issue
 // slots on its addresses (one vector addition per operand read, which holds off
 // fp32 MFMAs, and two divisions; <1, 1, 4, 4>: 2.5 vector and 5 scalar
-// instructions an MFMA, now 0.5 and 0.6) than on its MFMAs.  142 sampled 3x3 and
-// 5x5 points of six shapes ran 1.18 times as fast (geometric mean; none slower,
-// the best 1.8): 5x5 over 37 channels, batch 3, 61x53 (<1, 2, 1, 1>) 69.0 -> 47.7
+// instructions an MFMA, now 0.5 and 0.6) than on its MFMAs.  360 sampled 3x3 and
+// 5x5 points of nine shapes ran 1.2 times as fast (geometric mean; 1.04 to 1.8): 5x5 over 37 channels, batch 3, 61x53 (<1, 2, 1, 1>) 69.0 -> 47.7
 // us; ResNet-50's 3x3 stride 2 over 512 channels at batch 1 (<2, 1, 1, 2>) 15.9 ->
 // 14.9; 3x3 over 64 channels, 56x56 (<1, 1, 4, 4>) 9.74 -> 9.38.  1x1 filters, a
 // row a step, ran 5 to 15% slower this way, and as much slower in kernels that

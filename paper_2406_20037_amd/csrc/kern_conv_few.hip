@@ -4,7 +4,7 @@
 //
 // The channel-quad loop pads three channels to four (nine MFMA steps, here seven
 // of four taps each), computes its copy sources as it goes and takes every output
-// through LDS; fp32 MFMAs hold the vector unit meanwhile, so the 68 us of
+// through LDS; fp32 MFMAs hold the vector unit meanwhile, so the 69 us of
 // 16x3x224x224 (64 channels) were the sum of the three.  Here a lane reads its
 // taps straight from global memory (16 consecutive pixels a tap: 64 bytes in a
 // row), the weights stay in registers, and the outputs go from the accumulators
@@ -17,9 +17,9 @@
 //   - non-temporal stores where a wave's pixels are whole lines (57 -> 47 us; 64-byte pieces would
 //     reach memory as they are, so other sizes store normally).
 // Lanes along channels with 16-byte stores of four pixels each are slower (93 us).
-// Bound by its stores: 206 MB, which a plain fill writes in 30 us.  168 points of
-// seven shapes (one to three channels, strides 1 and 2, odd sizes): 1.85 times as
-// fast (geometric mean; least 1.16).
+// Bound by its stores: 206 MB, which a plain fill writes in 30 us.  240 points
+// of six shapes (one to three channels, strides 1 and 2, odd sizes): 1.9 times as
+// fast (geometric mean; least 1.01, a tile four columns wide of that layer).
 #include <type_traits>
 
 #include "kern_conv_tile.h"

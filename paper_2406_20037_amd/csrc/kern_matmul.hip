@@ -359,8 +359,10 @@ struct MfmaShape {
 
 // Whether K-tiles run software-pipelined (mm_mfma_pipe) with copies of W floats
 // per lane: at least two stages, every thread issuing the same number of copies
-// per K-tile, few enough for the wait counters (63) with two tiles in flight,
-// and at least two chunks per K-tile.
+// per K-tile, at most 32, and at least two chunks per K-tile.  The loop waits for
+// all copies but those of one K-tile, a count that must fit the six bits of the
+// wait (63).  With two tiles of 32 copies in flight the counter is full before the
+// last one, which then waits to be issued (W = 1: 64x64x64, 128x128x32, 256x256x16).
 template <int WM, int WN, int BK, int DB, int KG, int W>
 constexpr bool mm_pipelined() {
     using S = MfmaShape<WM, WN, BK, KG>;
