@@ -12,7 +12,9 @@
 //
 // That holds output by output, for every finite input: a workgroup whose
 // operands or outputs lie where it would not runs its tile again on fp32 MFMAs
-// (kExact and what follows it, below).
+// (kExact and what follows it, below).  Sums of bf16 values in place of fp32 operands:
+// Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype
+// For Higher-Precision Computations", ARITH 2019.
 //
 // A workgroup computes the tile of the fp32 program (conv_mfma2): tk channels x
 // th * tw pixels, four waves of 32 TB channels x 32 NB pixels.  Its reduction
@@ -22,16 +24,21 @@
 // splitting is done once per element instead of once per tap and wave.  An MFMA
 // step takes two taps (one per half-wave); the tenth tap is zero weights.
 //
-// What bounds it: the matrix cores at the clock that load leaves (1.9 GHz; the
-// library's bf16 product of 8192^2 matrices runs 1.13 PFLOP/s on the same card,
-// this loop 1.16 on 16x64x224x224, the padded tap included).  fp32 MFMAs hold
-// the vector unit, bf16 ones do not: 64 vector instructions between 32 of them
-// cost nothing, but only between MFMAs of the same wave, so the next stage is
-// split between the MFMAs of this one and kept in registers until the planes
-// in LDS are free.  Splitting it after the loop instead: 28x28x512 392 us, this
-// way 361.  VGG-16 at batch 16, against the fp32 program of the same schedule:
-// 64x224x224 532 -> 336 us, 512x28x28 (8 reduction splits, their reduce
-// included) 571 -> 351, 512x14x14 (16 splits) 177 -> 131.
+// What bounds it: two waves a SIMD with two barriers a stage and operands read
+// from LDS.  The matrix cores are busy for 58% of the cycles on 16x64x224x224, 60%
+// on 16x512x28x28 (8 splits) and 42% on 16x256x56x56 in bands of 128 pixels (a wave
+// of 64 x 32 reads 9 operands for 12 MFMAs, one of 64 x 64 12 for 24); bank
+// conflicts are 19 to 31% of the LDS-active cycles.  With the padded tap the first
+// runs 1.16 PFLOP/s of bf16 products; the library's product of 8192^2 matrices
+// 1.40 on the same card.  fp32 MFMAs hold the vector unit, bf16 ones do not: 64
+// vector instructions between 32 of them cost nothing, but only between MFMAs of
+// the same wave, so the next stage is split between the MFMAs of this one and kept
+// in registers until the planes in LDS are free (splitting it after the loop, when
+// this was tried: 28x28x512 392 us against 361).  VGG-16 at batch 16, against the
+// fp32 program of the same schedule: 64x224x224 532 -> 338 us, 512x28x28 (8
+// reduction splits, their reduce included) 571 -> 348, 512x14x14 (16 splits)
+// 177 -> 130.  The LDS it reserves is what the point's geometry states, the double
+// buffer of the fp32 program, which with large chunks is more than it uses.
 #include <type_traits>
 
 #include "kern_conv_tile.h"
@@ -462,8 +469,8 @@ extern const void *g_conv_split[kConvSplitSlots];
 namespace {
 
 // Two waves per SIMD (256 registers): the operands of a step are read while the
-// step before multiplies.  Three waves without that ran slower (28x28x512:
-// 363 us against 379 us; 14x14x512: 137 us against 147 us).
+// step before multiplies.  Three waves without that ran slower when it was tried
+// (28x28x512 379 us against 363, 14x14x512 147 against 137).
 struct Registrar {
     Registrar() {
         g_conv_split[0] = reinterpret_cast<const void *>(&conv_split<1, 1>);

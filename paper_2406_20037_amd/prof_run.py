@@ -24,7 +24,8 @@ def main(argv=None):
     ap = argparse.ArgumentParser()
     ap.add_argument("--workload", default="matmul_1024",
                     help="a single-kernel workload, a network layer (resnet50:NAME, vgg16:NAME) "
-                         "or a conv shape (conv:N,C,H,W,K,R,S,stride,pad; He-normal inputs)")
+                         "or a shape (conv:N,C,H,W,K,R,S,stride,pad with He-normal inputs, "
+                         "matmul:M,N,K with U[-1, 1) ones)")
     ap.add_argument("--sched", help="knob=value,... (every axis)")
     ap.add_argument("--mfma-ceiling", action="store_true",
                     help="launch the library's pure-MFMA calibration kernel --iters times "
@@ -57,6 +58,9 @@ def main(argv=None):
     if args.workload.startswith("conv:"):   # any conv shape: conv:N,C,H,W,K,R,S,stride,pad
         op, shape = wl.OP_CONV, tuple(int(v) for v in args.workload[5:].split(","))
         kind = "he"
+    elif args.workload.startswith("matmul:"):
+        op, shape = wl.OP_MATMUL, tuple(int(v) for v in args.workload[7:].split(","))
+        kind = "uniform"
     elif ":" in args.workload:        # a network layer, e.g. vgg16:L6_256_256_56
         net, layer = args.workload.split(":", 1)
         table = {"resnet50": wl.RESNET50, "vgg16": wl.VGG16}[net]

@@ -14,13 +14,15 @@ from synthdata import workloads as wl
 ROOT = pathlib.Path(__file__).resolve().parent.parent
 PROFILES = ROOT / "profiles"
 CMD = re.compile(r"prof_run --workload (\S+) --sched (\S+)")
-OURS = re.compile(r"^\| `(conv_valu|conv_mfma2?|mm_valu|mm_mfma|split_reduce_kernel|"
-                  r"mfma_ceiling_kernel)[<(]")
+OURS = re.compile(r"^\| `(conv_valu|conv_mfma2?|conv_split|conv_few|mm_valu|mm_mfma|mm_rows|"
+                  r"split_reduce_kernel|mfma_ceiling_kernel)[<(]")
 
 
 def resolve(workload):
     if workload.startswith("conv:"):
         return wl.OP_CONV, tuple(int(v) for v in workload[5:].split(","))
+    if workload.startswith("matmul:"):
+        return wl.OP_MATMUL, tuple(int(v) for v in workload[7:].split(","))
     if ":" in workload:
         net, layer = workload.split(":", 1)
         table = {"resnet50": wl.RESNET50, "vgg16": wl.VGG16}[net]
