@@ -76,6 +76,8 @@ def traffic_key(kernel: str, sched: str, shape=None) -> str:
             parts[pos] = "*"
         name = f"{fam}<{', '.join(parts)}>"
     kept = [kv for kv in sched.split(",") if kv and not kv.startswith("unroll=")]
+    if name.startswith("conv_split"):        # loads 4 bytes a lane, whatever vec
+        kept = [kv for kv in kept if not kv.startswith("vec=")]
     kv = dict(k.split("=", 1) for k in kept)
     if kv.get("mfma") == "3" and "th" in kv and "tw" in kv:
         npx = int(kv["th"]) * int(kv["tw"])
