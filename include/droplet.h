@@ -79,8 +79,8 @@ typedef struct ds_space ds_space;
  * LDS) and the rest across workgroups; 3 the same over band tiles: th * tw
  * consecutive pixels of the output flattened over (image, row, column).  Only
  * band tiles may reach past the output's height or width.  3x3 points of mfma 2
- * and 3 at unroll depth 1 over whole groups of eight channels compute their
- * fp32 products as six bf16 MFMAs of operands split into three bf16 values
+ * and 3 at unroll depth 1 over whole groups of eight channels compute, where that
+ * is faster, their fp32 products as six bf16 MFMAs of operands split into three bf16 values
  * (24 bits; no less precise than the fp32 MFMA).  Tiles that hold infinities, NaN
  * or operands too small for that are computed again with fp32 MFMAs in the same
  * launch, so the time of such a launch depends on its data.  matmul axes: bm,
