@@ -122,7 +122,7 @@ struct MatmulArgs {
     int pipe;             // floats per lane of the pipelined MFMA loop's copies: 4 when rows
                           //    of A and B are whole aligned 16-byte groups, else 1 (0:
                           //    staged through registers)
-    int uf;               // mm_rows: rows of B in flight per thread (1 to 4)
+    int uf;               // mm_rows: unroll factor of the reduction loop
     float *part;          // ks > 1: split z writes its partial C at part + z * M*N
     int gm;               // tile rows per group of the XCD tile order (mm_group_rows)
 };

@@ -655,10 +655,7 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         plan.y_elems = int64_t(a.M) * a.N;
         if (mm_few_rows(a.M, a.K, mfma, bn, bk, a.ks, dbuf, a.vecB)) {
             const int lr = a.M > 2 ? 2 : a.M - 1;
-            // 256 rows of B in flight a workgroup (4096x4096 and one row, 1, 2, 4, 8 a
-            // thread: ks 8 13.9 14.6 15.2 15.6 us, ks 4 14.1 13.4 14.0 13.7, ks 2 21.2 14.9
-            // 13.3 14.0; 2048x1000 3.7 at 8 x 1, 3.8 at 4 x 2 and 2 x 4)
-            a.uf = std::min(g.unroll_eff, 8 / a.ks);
+            a.uf = g.unroll_eff;
             plan.func = g_mm_rows[lr];
             plan.nparams = 6;
             plan.params[5] = 1 << lr;

@@ -799,8 +799,12 @@ __global__ __launch_bounds__(1024) void mm_rows(MatmulArgs a) {
     };
     // every thread has `left` rows, the first K % step of them one more
     int k = r0, left = a.K / step;
+    // 256 rows of B in flight a workgroup (4096x4096 and one row, 1, 2, 4, 8 a thread: ks
+    // 8 13.9 14.6 15.2 15.6 us, ks 4 14.1 13.4 14.0 13.7, ks 2 21.2 14.9 13.3 14.0; 2048x1000
+    // 3.7 at 8 x 1, 3.8 at 4 x 2 and 2 x 4)
+    const int flight = min(a.uf, 1024 / int(blockDim.x));
     auto blocks = [&]<int D>(std::integral_constant<int, D> d) {
-        if (a.uf < D) return;
+        if (flight < D) return;
         for (; left >= D; left -= D, k += D * step) rows(d, k);
     };
     blocks(std::integral_constant<int, 4>{});
