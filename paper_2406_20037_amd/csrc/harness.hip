@@ -630,14 +630,14 @@ int make_plan(const ds_sched *s, const float *x, const float *w, float *y, Plan 
         a.vecB = vec == 4 && (a.N % 4 == 0) && (reinterpret_cast<uintptr_t>(w) % 16 == 0);
         a.direct = a.vecA && a.vecB && a.M % bm == 0 && a.N % bn == 0 && a.K % bk == 0;
         // 4-byte copies lose to loads through registers where the checked copies of a
-        // ragged last K-tile are most of a short loop: where the loads take one
-        // operand 16 bytes at a time (64x2000x129: 9.3 us against 7.4 at 3 K-tiles, 6.9
-        // against 6.7 at 5, even at 9), and of 4-byte loads where that tile is the
-        // only one (95 sampled points: 1.3% slower in the mean, the worst 18%; with
-        // two tiles 3% faster)
+        // ragged last K-tile are most of a short loop.  4872 sampled points of 348 shapes,
+        // both ways: where the loads take one operand 16 bytes at a time, the copies are
+        // 3% slower in the mean with one K-tile (the worst 20%), even with two (15%), 2%
+        // faster with three (9%) and 4 to 11% faster from four on (4%); where they take
+        // none so, 1% slower with one (17%) and 3 to 21% faster from two on.
         const bool reach = int64_t(std::min(a.M, bm)) * a.K < (int64_t(1) << 30) &&
                            int64_t(bk) * a.N < (int64_t(1) << 30);
-        const bool brief = a.K % bk != 0 && a.kps < (a.vecA != a.vecB ? 8 : 2);
+        const bool brief = a.K % bk != 0 && a.kps < (a.vecA != a.vecB ? 4 : 2);
         a.pipe = a.vecA && a.vecB ? 4 : brief ? 0 : 1;
         if (!reach) a.pipe = 0;
         a.gm = mm_group_rows(a.tiles_m, a.tiles_n, a.ks, bm, bn);
